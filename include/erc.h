@@ -85,7 +85,8 @@ typedef struct {
 /* Accumulate into R instead of overwriting it (resume, column-range sharding). */
 #define ERC_ACCUMULATE 1u
 /* Time every SpMM launch with a pair of HIP events on the caller's stream and report
- * the sum in erc_solve_info.ms_spmm / spmm_timed (adds two event records per launch). */
+ * the sum in erc_solve_info.ms_spmm / spmm_timed (adds two event records per launch; small
+ * graphs are then solved by those launches instead of a single one). */
 #define ERC_PROFILE_SPMM 2u
 /* Solve with Jacobi-preconditioned CG (M^-1 = diag(1 / (d_i + delta)), d_i = sum_j w_ij)
  * instead of the paper's plain column-wise CG (Section 3.1.3).  Same stopping test
@@ -97,7 +98,8 @@ typedef struct {
  * check_every iterations is captured once into a HIP graph (on a stream the handle
  * owns) and replayed on the caller's stream, which removes most of the per-launch
  * overhead on small graphs; the kernels, their order and the results are the same.
- * ERC_PROFILE_SPMM implies this flag (its events sit between the launches). */
+ * ERC_PROFILE_SPMM implies this flag (its events sit between the launches).  It changes
+ * nothing on small graphs, whose solves are one launch (see erc_resistance). */
 #define ERC_NO_GRAPH 8u
 /* Enqueue, after every CG update, the exact stopping test that runs only when every
  * active column is predicted to stop (it saves the one SpMM that would otherwise follow
@@ -197,6 +199,10 @@ erc_status erc_workspace_bytes(erc_handle h, int32_t k_block, size_t* bytes);
  * where Z solves (L + delta I) Z = B^T W^{1/2} Q column by column with CG
  * (or += with ERC_ACCUMULATE).  ws_dev is device memory of >= erc_workspace_bytes
  * bytes.  The call blocks until the stream has drained.
+ * Graphs of up to 32,768 nodes (16,384 for ERC_F64) with at most 6 MB of positions and
+ * weights and few long rows are solved by one launch for all columns that the workspace
+ * holds, one workgroup per column, instead of launches per CG iteration; ERC_PROFILE_SPMM
+ * keeps the latter, as there is no SpMM launch to time in the former.
  * Returns ERC_E_NOT_CONVERGED (R still written) when a column hit max_iter above tol,
  * ERC_E_NUMERIC on a CG breakdown or when some R_e ends <= 0 or non-finite (curvature
  * needs R_e > 0). */

@@ -30,6 +30,41 @@ struct alignas(16) LightRow {
   int32_t deg;  // rowptr[row + 1] - rowptr[row]
 };
 
+// Plan of the resident CG (erc_resident.hip), kept for graphs of up to a few ten thousand
+// nodes.  Rows sit at positions 0 .. n-1: first the rows of more than kResHeavy entries,
+// then the others by decreasing degree.  Thread t of a workgroup of nt threads owns the
+// positions t, t + nt, ... (one per slot).  The entries of the 64 rows of
+// wavefront v's slot s are stored as quads off[v * rpt + s] .. off[v * rpt + s + 1] - 1:
+// quad t of lane l holds four (position, weight) pairs at (t * 64 + l) * 4, padded with the
+// row's own position and weight zero.
+constexpr int kResHeavy = 128;   // rows above this many entries are summed by whole wavefronts
+constexpr int kResChunk = 256;  // in chunks of this many entries
+constexpr int kResPadQuads = 4;  // readable quads past the last one
+struct ResPlan {
+  int32_t on;             // 0: no such plan; else where q is kept: 1 in LDS, 2 in memory
+  int32_t nt;             // threads of a workgroup
+  int32_t rpt;            // slots
+  int32_t nheavy;         // positions below this are rows of more than kResHeavy entries
+  int32_t nchunk;         // chunks of those rows
+  int32_t quads;          // most quads of one wavefront
+  const int32_t* row;     // rpt * nt: row at each position (0 beyond n)
+  const uint16_t* pos;    // n: position of each row
+  const int32_t* off;     // nt / 64 * rpt + 1
+  const uint16_t* idx;    // quads x 64 x 4
+  const void* w;          // the same shape, working precision (weighted graphs)
+  const uint16_t* cpos;   // nnz: position of each CSR entry's column (the chunks read it)
+  const int32_t* hpos;    // nchunk: position of each chunk's row
+  const int32_t* hbeg;    // nchunk: first entry in CSR
+  const int32_t* hlen;    // nchunk
+  const int32_t* hc0;     // nheavy + 1: first chunk of each long row
+};
+
+// What the resident CG reports for each column.
+struct ResOut {
+  double rr, rho0;
+  int32_t iters, active, status, pad;
+};
+
 struct DevGraph {
   int32_t n;
   int64_t nnz;
@@ -65,6 +100,8 @@ struct DevGraph {
   const int32_t* piece_row;
   const int64_t* piece_beg;  // CSR position
   const int64_t* piece_end;
+
+  ResPlan res;
 };
 
 // Per-column CG state of one block, in the workspace.
@@ -109,7 +146,7 @@ struct Work {
   double* part;      // block partials of the SpMM / RHS launch: grid x 3 x kb pairs
   double* part_u;    // block partials of the update launch: grid_upd x kb pairs
   Tree tree;         // tickets and levels of the small finishing launches
-  double* out;       // small fp64 output area (totals for the host)
+  unsigned long long* bad;  // count of resistances that are <= 0 or not finite
   void* minv;        // n: 1 / (d_i + delta) in the working precision (Jacobi variant)
   int pc;            // 1: Jacobi-preconditioned CG, 0: plain CG
   int fin2;          // 1: enqueue the early exact stopping test after each update
@@ -121,6 +158,11 @@ hipError_t launch_fill_u32(uint32_t* p, uint32_t v, int64_t count, hipStream_t s
 hipError_t launch_fill_f64(double* p, double v, int64_t count, hipStream_t s);
 hipError_t launch_rhs(const DevGraph& g, const Work& w, erc_dtype dt, int K, int col0, int ncols,
                       uint64_t base, double inv_sqrt_k, double tol, hipStream_t s);
+// the right-hand sides alone, into w.r (no CG state)
+hipError_t launch_rhs_only(const DevGraph& g, const Work& w, erc_dtype dt, int K, int col0,
+                           int ncols, uint64_t base, double inv_sqrt_k, hipStream_t s);
+// tickets and counters to zero, the constant gate to one
+hipError_t launch_prepare(const Work& w, hipStream_t s);
 hipError_t launch_spmm(const DevGraph& g, const Work& w, erc_dtype dt, double delta,
                        const void* p, const void* r, void* q, const int32_t* gate,
                        hipStream_t s);
@@ -139,6 +181,23 @@ hipError_t launch_edge_kappa(const DevGraph& g, const double* R, const double* p
                              hipStream_t s);
 hipError_t launch_endpoints(const DevGraph& g, int32_t* u, int32_t* v, hipStream_t s);
 hipError_t launch_eids(const DevGraph& g, int32_t* out, hipStream_t s);
+
+// Resident CG (erc_resident.hip).  Workgroup size and slots for n rows (slots 0: too many
+// rows).
+struct ResForm {
+  int nt, rpt;
+};
+ResForm res_form(erc_dtype dt, int64_t n);
+// Where the resident CG of n rows keeps q: 1 in the LDS, 2 in global memory, 0 if the plan
+// does not fit a CU at all; *lds receives the launch's dynamic LDS bytes.
+int res_q_place(ResForm f, int64_t n, int nchunk, erc_dtype dt, size_t* lds);
+// The plan's device-side arrays; M^-1 by position; the solve of the ncols columns of an
+// n x kb block whose right-hand sides are in y (solutions replace them).
+hipError_t launch_res_fill(const DevGraph& g, erc_dtype dt, hipStream_t s);
+hipError_t launch_res_minv(const DevGraph& g, erc_dtype dt, double delta, void* minv, hipStream_t s);
+hipError_t launch_resident(const DevGraph& g, erc_dtype dt, void* y, void* q, int kb, int ncols,
+                           double delta, double tol2, int max_iter, const void* minv_pos,
+                           ResOut* out, hipStream_t s);
 
 struct SampleWork {
   double* part_mm;   // grid x 3 block partials (-kappa_min, kappa_max, non-finite flag),

@@ -84,6 +84,20 @@ constexpr int kMaxGridEd = 8192;
 constexpr int kSampleGrid = 1024;
 static_assert(int64_t{kSampleGrid} * 4 * 8 + 3 * 256 <= static_cast<int64_t>(kStaticScratchBytes),
               "the sampling scratch at the grid cap must fit the fixed scratch");
+// Largest operator stream (position and weight bytes per column and iteration) and number of
+// long-row chunks of the resident CG.  A workgroup streams the operator from the L2 by itself
+// and its wavefronts take the chunks in turn, where the block kernels take 30-50 us an
+// iteration on small graphs whatever the size.  Time of the block kernels (graph replay)
+// over that of the resident CG for 16 / 64 / 256 columns in blocks of 64:
+//   2000 rows, 120,000 entries, fp32 unit              2.9 / 2.9 / 8.5
+//   16,000 rows, 320,000 entries, fp32 weighted        1.8 / 1.9 / 6.2   (1.9 MB)
+//   16,000 rows, 320,000 entries, fp64 weighted        1.2 / 1.2 / 2.3   (3.2 MB)
+//   30,000 rows, 990,000 entries, fp32 weighted        0.98 / 1.1 / 2.1  (5.9 MB)
+//   12,000 rows, 190,000 entries, power-law, fp64 weighted   1.1 / 1.7 / 2.9
+// and without the limits, at 9.6 MB about 0.6-0.7 of the block kernels' speed for 16 and 64
+// columns, at 1600 and 4000 chunks 0.4-0.7 and 0.2-0.4.
+constexpr int64_t kResMaxStream = 6000000;
+constexpr int64_t kResMaxChunks = 256;
 constexpr int kDefaultCheck = 16;
 // Neighbour-row bytes one SpMM gathers (nnz * kb * element size) above which each CG
 // iteration also enqueues the early stopping test: 4 GB is about half a millisecond of
@@ -101,9 +115,11 @@ struct Shape {
   int64_t heavy;     // rows with degree above this are block tasks
   int64_t chunk;     // block tasks are at most this long
   int64_t ntask_max, nmega_max, nslot_max, npiece_max;
+  ResForm res;       // form of the resident CG (0 slots: the graph is too large for it)
+  int64_t quads_max, hchunk_max;
 };
 
-Shape make_shape(int64_t n, int64_t nnz) {
+Shape make_shape(int64_t n, int64_t nnz, bool weighted, erc_dtype dt) {
   Shape s{};
   s.n = n;
   s.nnz = nnz;
@@ -128,13 +144,22 @@ Shape make_shape(int64_t n, int64_t nnz) {
   s.nmega_max = nnz / s.chunk + 1;
   s.nslot_max = 2 * (nnz / s.chunk) + 1;
   s.npiece_max = n + s.m / kPiece + 1;
+  if (nnz * (2 + (weighted ? static_cast<int64_t>(dsize(dt)) : 0)) <= kResMaxStream) s.res = res_form(dt, n);
+  if (s.res.rpt > 0) {
+    // rows run by decreasing degree, so 64 x (longest row) summed over the wavefronts' slots
+    // is at most 64 rows of kResHeavy entries plus nnz; each slot rounds up to four entries
+    s.quads_max = ceil_div(64 * kResHeavy + nnz + int64_t{3} * s.res.nt * s.res.rpt, 256) + kResPadQuads;
+    s.hchunk_max = kResMaxChunks;
+  }
   return s;
 }
 
 // Byte layout of the graph buffer.
 struct GraphLayout {
   int64_t rowptr, col, w, eid, sw, ubase, deg, light, wave_lo, task_row, task_mega, task_chunk,
-      task_beg, task_end, mega_row, mega_nchunk, mega_chunk0, piece_row, piece_beg, piece_end, total;
+      task_beg, task_end, mega_row, mega_nchunk, mega_chunk0, piece_row, piece_beg, piece_end,
+      res_row, res_pos, res_off, res_idx, res_w, res_cpos, res_hpos, res_hbeg, res_hlen, res_hc0,
+      total;
 };
 
 GraphLayout graph_layout(const Shape& s, bool weighted, erc_dtype dt) {
@@ -165,6 +190,19 @@ GraphLayout graph_layout(const Shape& s, bool weighted, erc_dtype dt) {
   L.piece_row = take(s.npiece_max * 4);
   L.piece_beg = take(s.npiece_max * 8);
   L.piece_end = take(s.npiece_max * 8);
+  if (s.res.rpt > 0) {
+    const int64_t sz = static_cast<int64_t>(dsize(dt));
+    L.res_row = take(int64_t{s.res.nt} * s.res.rpt * 4);
+    L.res_pos = take(s.n * 2);
+    L.res_off = take((int64_t{s.res.nt / 64} * s.res.rpt + 1) * 4);
+    L.res_hpos = take(s.hchunk_max * 4);
+    L.res_hbeg = take(s.hchunk_max * 4);
+    L.res_hlen = take(s.hchunk_max * 4);
+    L.res_hc0 = take((s.hchunk_max + 1) * 4);
+    L.res_idx = take(s.quads_max * 512);
+    L.res_w = take(weighted ? s.quads_max * 256 * sz : 0);
+    L.res_cpos = take(s.nnz * 2);
+  }
   L.total = off;
   return L;
 }
@@ -374,7 +412,102 @@ struct Plan {
   int32_t nslot = 0;
   std::vector<int32_t> piece_row;
   std::vector<int64_t> piece_beg, piece_end;
+  // resident CG (empty if the graph has no such plan)
+  std::vector<int32_t> res_row, res_off, res_hpos, res_hbeg, res_hlen, res_hc0;
+  std::vector<uint16_t> res_pos;
+  int32_t res_nheavy = 0;
+  int res_on = 0;
 };
+
+// Positions, slots and long-row chunks of the resident CG (see ResPlan).
+void build_res_plan(const erc_graph_desc* d, const Shape& s, Plan* P) {
+  const int64_t n = d->n;
+  const int64_t* rp = d->rowptr;
+  const int64_t nt = s.res.nt, npos = nt * s.res.rpt;
+  const int nw = s.res.nt / 64;
+  // rows above kResHeavy entries first, then the others by decreasing degree, ascending ids
+  // among equal ones
+  std::vector<int64_t> start(kResHeavy + 2, 0);  // by kResHeavy - degree + 1; 0: long rows
+  auto key = [&](int64_t i) {
+    const int64_t dg = rp[i + 1] - rp[i];
+    return dg > kResHeavy ? int64_t{0} : kResHeavy - dg + 1;
+  };
+  for (int64_t i = 0; i < n; ++i) ++start[key(i)];
+  P->res_nheavy = static_cast<int32_t>(start[0]);
+  int64_t at = 0;
+  for (int64_t& x : start) {
+    const int64_t c = x;
+    x = at;
+    at += c;
+  }
+  P->res_row.assign(npos, 0);
+  for (int64_t i = 0; i < n; ++i) P->res_row[start[key(i)]++] = static_cast<int32_t>(i);
+  // Slices of 64 rows: the first ones (long rows) and the last (not full) stay, the others go,
+  // longest first, to the wavefront with the fewest quads so far that has a slice left
+  {
+    const int64_t first = ceil_div(P->res_nheavy, 64), last = n / 64;  // slices [first, last) move
+    std::vector<int64_t> load(nw, 0), slot(nw, 0), have(nw, 0);
+    auto quads = [&](int64_t k) {  // a slice's quads: its first row of at most kResHeavy entries
+      const int64_t p = std::max<int64_t>(k * 64, P->res_nheavy);
+      const int64_t dg = p < n ? rp[P->res_row[p] + 1] - rp[P->res_row[p]] : 0;
+      return (dg + 3) / 4;
+    };
+    for (int64_t k = 0; k < ceil_div(n, 64); ++k)
+      if (k < first || k >= last) load[k % nw] += quads(k);
+      else ++have[k % nw];
+    const std::vector<int32_t> sorted = P->res_row;
+    for (int w = 0; w < nw; ++w) slot[w] = ceil_div(first - w, nw);
+    for (int64_t k = first; k < last; ++k) {
+      int best = -1;
+      for (int w = 0; w < nw; ++w)
+        if (have[w] > 0 && (best < 0 || load[w] < load[best])) best = w;
+      load[best] += quads(k);
+      --have[best];
+      const int64_t cell = slot[best]++ * nw + best;
+      std::copy(sorted.begin() + k * 64, sorted.begin() + k * 64 + 64, P->res_row.begin() + cell * 64);
+    }
+  }
+  P->res_pos.resize(n);
+  for (int64_t p = 0; p < n; ++p) P->res_pos[P->res_row[p]] = static_cast<uint16_t>(p);
+  P->res_off.assign(int64_t{s.res.nt / 64} * s.res.rpt + 1, 0);
+  int32_t quads = 0;
+  for (int w = 0; w < nw; ++w) {
+    for (int slot = 0; slot < s.res.rpt; ++slot) {
+      int64_t longest = 0;
+      for (int l = 0; l < 64; ++l) {
+        const int64_t p = slot * nt + w * 64 + l;
+        if (p < P->res_nheavy || p >= n) continue;
+        const int32_t i = P->res_row[p];
+        longest = std::max(longest, rp[i + 1] - rp[i]);
+      }
+      quads += static_cast<int32_t>((longest + 3) / 4);
+      P->res_off[w * s.res.rpt + slot + 1] = quads;
+    }
+  }
+  int64_t chunks = 0;
+  for (int32_t p = 0; p < P->res_nheavy; ++p) {
+    const int32_t i = P->res_row[p];
+    chunks += ceil_div(rp[i + 1] - rp[i], kResChunk);
+  }
+  if (chunks > kResMaxChunks) {
+    P->res_row.clear();
+    return;
+  }
+  for (int32_t p = 0; p < P->res_nheavy; ++p) {
+    const int32_t i = P->res_row[p];
+    P->res_hc0.push_back(static_cast<int32_t>(P->res_hpos.size()));
+    for (int64_t b = rp[i]; b < rp[i + 1]; b += kResChunk) {
+      P->res_hpos.push_back(p);
+      P->res_hbeg.push_back(static_cast<int32_t>(b));
+      P->res_hlen.push_back(static_cast<int32_t>(std::min<int64_t>(kResChunk, rp[i + 1] - b)));
+    }
+  }
+  P->res_hc0.push_back(static_cast<int32_t>(P->res_hpos.size()));
+  // the long rows' chunk sums must fit the LDS beside the search direction
+  size_t lds = 0;
+  P->res_on = res_q_place(s.res, n, static_cast<int>(P->res_hpos.size()), d->solve_dtype, &lds);
+  if (P->res_on == 0) P->res_row.clear();
+}
 
 void build_plan(const erc_graph_desc* d, const Canon& c, const Shape& s, Plan* P) {
   const int64_t n = d->n;
@@ -460,13 +593,14 @@ void build_plan(const erc_graph_desc* d, const Canon& c, const Shape& s, Plan* P
       P->piece_end.push_back(std::min(rp[u + 1], b + kPiece));
     }
   }
+  if (s.res.rpt > 0) build_res_plan(d, s, P);
 }
 
 // Workspace layout for a padded block width.
 struct WorkLayout {
   int64_t z, r, p, q, chunkbuf, mega_dots, rho, rr, rho0, thr, alpha, beta, active,
       iters, status, n_active, upd_pending, pred_done, nspmm, fin_ctr, one, part, part_u, lvl0, lvl1, lvl2, tick, out, minv,
-      total;
+      res_out, total;
   int grid_rhs, grid_upd, grid_ed, grid_tree;
 };
 
@@ -556,7 +690,8 @@ WorkLayout work_layout(const erc_graph_s* h, int kb) {
   L.lvl2 = take(ceil_div(kMaxTreeGrid, kTreeFan * kTreeFan) * nval * 8);
   L.tick = take(tree_ticks(kMaxTreeGrid) * 4);
   L.out = take(8 * 8);
-  L.minv = take(h->n * s);
+  L.minv = take(std::max(h->n, int64_t{h->dg.res.nt} * h->dg.res.rpt) * s);
+  L.res_out = take(h->dg.res.on ? int64_t{256} * sizeof(ResOut) : 0);
   L.total = off;
   return L;
 }
@@ -592,7 +727,7 @@ Work carve_work(const erc_graph_s* h, int kb, void* ws, const WorkLayout& L, int
   w.tree.lvl1 = reinterpret_cast<double*>(b + L.lvl1);
   w.tree.lvl2 = reinterpret_cast<double*>(b + L.lvl2);
   w.tree.tick = reinterpret_cast<uint32_t*>(b + L.tick);
-  w.out = reinterpret_cast<double*>(b + L.out);
+  w.bad = reinterpret_cast<unsigned long long*>(b + L.out);
   w.minv = b + L.minv;
   w.pc = pc;
   // The early stopping test after each update (a third finishing launch, which exits at
@@ -606,12 +741,10 @@ Work carve_work(const erc_graph_s* h, int kb, void* ws, const WorkLayout& L, int
   return w;
 }
 
-// Zero the tickets and set the constant-one gate (fill kernels, so a captured stream
-// records no memset node).
-erc_status prepare_work(const erc_graph_s* h, const Work& w, const WorkLayout& L, hipStream_t s) {
-  ERC_HIP(launch_fill_u32(w.tree.tick, 0u, tree_ticks(kMaxTreeGrid), s));
-  ERC_HIP(launch_fill_u32(reinterpret_cast<uint32_t*>(w.cs.fin_word), 0u, 2, s));
-  ERC_HIP(launch_fill_u32(reinterpret_cast<uint32_t*>(w.cs.one), 1u, 1, s));
+// Zero the tickets and counters and set the constant-one gate (a fill kernel, so a captured
+// stream records no memset node).
+erc_status prepare_work(const Work& w, hipStream_t s) {
+  ERC_HIP(launch_prepare(w, s));
   return ERC_OK;
 }
 
@@ -819,6 +952,56 @@ erc_status solve_block(erc_graph_s* h, const erc_solve_params* p, const Work& w,
   return ERC_OK;
 }
 
+// The columns of [c0, c0 + nc) by the resident CG: right-hand sides, one launch that solves
+// them all, then (if R != nullptr) the edge distances.  The solve needs one n x nc array, so
+// that the four of the caller's workspace hold up to four blocks' columns at once.  w keeps
+// the solutions' place and width on return.  Ends with the stream drained.
+erc_status solve_resident(erc_graph_s* h, const erc_solve_params* p, Work* w, const WorkLayout& L,
+                          void* ws, int c0, int nc, double* R, int accumulate, int32_t* iters_out,
+                          BlockStats* st, hipStream_t s) {
+  const double inv_sqrt_k = 1.0 / std::sqrt(static_cast<double>(p->K_total));
+  ResOut* out = reinterpret_cast<ResOut*>(static_cast<char*>(ws) + L.res_out);
+  w->kb = padded_width(h->dt, nc);
+  w->r = w->z = static_cast<char*>(ws) + L.z;
+  ERC_HIP(hipEventRecord(h->ev[0], s));
+  if (w->pc) ERC_HIP(launch_res_minv(h->dg, h->dt, p->delta, w->minv, s));
+  ERC_HIP(launch_rhs_only(h->dg, *w, h->dt, p->K_total, c0, nc, splitmix_first(p->seed), inv_sqrt_k, s));
+  ERC_HIP(hipEventRecord(h->ev[1], s));
+  // the workspace's four n x kb arrays follow each other: the solution's columns, then q's
+  char* q = static_cast<char*>(w->z) + h->n * w->kb * static_cast<int64_t>(dsize(h->dt));
+  ERC_HIP(launch_resident(h->dg, h->dt, w->z, h->dg.res.on == 2 ? q : nullptr, w->kb, nc, p->delta, p->tol * p->tol, p->max_iter,
+                          w->pc ? w->minv : nullptr, out, s));
+  ERC_HIP(hipEventRecord(h->ev[2], s));
+  if (R != nullptr) ERC_HIP(launch_edge_dist(h->dg, *w, h->dt, R, accumulate, s));
+  ERC_HIP(hipEventRecord(h->ev[3], s));
+  ResOut* ho = reinterpret_cast<ResOut*>(h->pinned + 8);
+  ERC_HIP(hipMemcpyAsync(ho, out, static_cast<size_t>(nc) * sizeof(ResOut), hipMemcpyDeviceToHost, s));
+  ERC_HIP(hipStreamSynchronize(s));
+  for (int c = 0; c < nc; ++c) {
+    const ResOut& o = ho[c];
+    st->iters_total += o.iters;
+    st->iters_max = std::max(st->iters_max, o.iters);
+    if (o.status != 0) st->breakdowns += 1;
+    else if (o.active != 0) st->unconverged += 1;
+    if (o.rho0 > 0.0) st->max_relres = std::max(st->max_relres, std::sqrt(o.rr / o.rho0));
+    if (iters_out) iters_out[c] = o.iters;
+  }
+  float a = 0, b = 0, c = 0;
+  ERC_HIP(hipEventElapsedTime(&a, h->ev[0], h->ev[1]));
+  ERC_HIP(hipEventElapsedTime(&b, h->ev[1], h->ev[2]));
+  ERC_HIP(hipEventElapsedTime(&c, h->ev[2], h->ev[3]));
+  st->ms_rhs += a;
+  st->ms_cg += b;
+  st->ms_accum += c;
+  return ERC_OK;
+}
+
+// Columns that one resident solve takes: as many as the workspace's four n x kb arrays hold
+// (once, or twice where q is in memory too) and the widest edge-distance kernel reads.
+int resident_cols(const erc_graph_s* h, int kb) {
+  return std::min(h->dg.res.on == 2 ? 2 * kb : 4 * kb, max_width(h->dt));
+}
+
 erc_status check_handle(const erc_graph_s* h) {
   if (h == nullptr) return fail(ERC_E_INVALID_ARG, "handle is NULL");
   return ERC_OK;
@@ -866,7 +1049,7 @@ erc_status erc_graph_bytes(const erc_graph_desc* desc, size_t* bytes) {
     erc_status st = check_desc(desc);
     if (st != ERC_OK) return st;
     if (bytes == nullptr) return fail(ERC_E_INVALID_ARG, "bytes is NULL");
-    const Shape s = make_shape(desc->n, desc->rowptr[desc->n]);
+    const Shape s = make_shape(desc->n, desc->rowptr[desc->n], desc->w != nullptr, desc->solve_dtype);
     *bytes = static_cast<size_t>(graph_layout(s, desc->w != nullptr, desc->solve_dtype).total);
     return ERC_OK;
   });
@@ -886,7 +1069,7 @@ erc_status erc_create(const erc_graph_desc* desc, void* dev_mem, size_t bytes, v
     if (st != ERC_OK) return st;
     const int64_t n = desc->n;
     const int64_t nnz = desc->rowptr[n];
-    const Shape s = make_shape(n, nnz);
+    const Shape s = make_shape(n, nnz, desc->w != nullptr, desc->solve_dtype);
     const bool weighted = desc->w != nullptr;
     const GraphLayout L = graph_layout(s, weighted, desc->solve_dtype);
     if (static_cast<int64_t>(bytes) < L.total)
@@ -895,7 +1078,9 @@ erc_status erc_create(const erc_graph_desc* desc, void* dev_mem, size_t bytes, v
     build_plan(desc, c, s, &P);
     if (static_cast<int64_t>(P.task_row.size()) > s.ntask_max ||
         static_cast<int64_t>(P.mega_nchunk.size()) > s.nmega_max ||
-        static_cast<int64_t>(P.piece_row.size()) > s.npiece_max || P.nslot > s.nslot_max)
+        static_cast<int64_t>(P.piece_row.size()) > s.npiece_max || P.nslot > s.nslot_max ||
+        (!P.res_row.empty() && (P.res_off.back() + kResPadQuads > s.quads_max ||
+                                static_cast<int64_t>(P.res_hpos.size()) > s.hchunk_max)))
       return fail(ERC_E_STATE, "internal: work plan exceeds its size bound");
     // weights in the working precision
     std::vector<float> wf;
@@ -952,12 +1137,32 @@ erc_status erc_create(const erc_graph_desc* desc, void* dev_mem, size_t bytes, v
       return cleanup(fail(ERC_E_DEVICE, "hipStreamCreateWithFlags failed"));
     char* base = static_cast<char*>(dev_mem);
     hipStream_t hs = static_cast<hipStream_t>(stream);
-    auto up = [&](int64_t off, const void* src, int64_t nbytes) -> hipError_t {
-      if (nbytes <= 0) return hipSuccess;
-      return hipMemcpyAsync(base + off, src, nbytes, hipMemcpyHostToDevice, hs);
-    };
     hipError_t e = hipSuccess;
     auto chk = [&](hipError_t x) { if (e == hipSuccess) e = x; };
+    // arrays that follow each other within kStage bytes go up in one copy, from a host buffer
+    // that lives until the stream is drained: a copy costs about 10 us whatever its size, and
+    // a small graph has some twenty arrays (2000 nodes: 0.75 -> 0.6 ms per erc_create)
+    constexpr int64_t kStage = 1 << 20;
+    std::vector<std::vector<char>> stages;
+    int64_t stage_at = 0;  // offset of the open stage
+    std::vector<char> open;
+    auto flush = [&]() {
+      if (open.empty()) return;
+      chk(hipMemcpyAsync(base + stage_at, open.data(), open.size(), hipMemcpyHostToDevice, hs));
+      stages.push_back(std::move(open));
+      open.clear();
+    };
+    auto up = [&](int64_t off, const void* src, int64_t nbytes) -> hipError_t {
+      if (nbytes <= 0) return hipSuccess;
+      if (!open.empty() && (off < stage_at + static_cast<int64_t>(open.size()) ||
+                            off + nbytes > stage_at + kStage))
+        flush();
+      if (nbytes > kStage / 2) return hipMemcpyAsync(base + off, src, nbytes, hipMemcpyHostToDevice, hs);
+      if (open.empty()) stage_at = off;
+      open.resize(off - stage_at);
+      open.insert(open.end(), static_cast<const char*>(src), static_cast<const char*>(src) + nbytes);
+      return hipSuccess;
+    };
     chk(up(L.rowptr, desc->rowptr, (n + 1) * 8));
     chk(up(L.col, desc->col, nnz * 4));
     if (weighted) chk(up(L.w, wsrc, nnz * static_cast<int64_t>(dsize(desc->solve_dtype))));
@@ -986,8 +1191,16 @@ erc_status erc_create(const erc_graph_desc* desc, void* dev_mem, size_t bytes, v
     chk(up(L.piece_row, P.piece_row.data(), np * 4));
     chk(up(L.piece_beg, P.piece_beg.data(), np * 8));
     chk(up(L.piece_end, P.piece_end.data(), np * 8));
-    if (e == hipSuccess) e = hipStreamSynchronize(hs);
-    if (e != hipSuccess) return cleanup(fail(ERC_E_DEVICE, std::string("graph upload: ") + hipGetErrorString(e)));
+    const bool res = !P.res_row.empty();
+    if (res) {
+      chk(up(L.res_row, P.res_row.data(), static_cast<int64_t>(P.res_row.size()) * 4));
+      chk(up(L.res_pos, P.res_pos.data(), n * 2));
+      chk(up(L.res_off, P.res_off.data(), static_cast<int64_t>(P.res_off.size()) * 4));
+      chk(up(L.res_hpos, P.res_hpos.data(), static_cast<int64_t>(P.res_hpos.size()) * 4));
+      chk(up(L.res_hbeg, P.res_hbeg.data(), static_cast<int64_t>(P.res_hbeg.size()) * 4));
+      chk(up(L.res_hlen, P.res_hlen.data(), static_cast<int64_t>(P.res_hlen.size()) * 4));
+      chk(up(L.res_hc0, P.res_hc0.data(), static_cast<int64_t>(P.res_hc0.size()) * 4));
+    }
     DevGraph& g = h->dg;
     g.n = static_cast<int32_t>(n);
     g.nnz = nnz;
@@ -1020,6 +1233,30 @@ erc_status erc_create(const erc_graph_desc* desc, void* dev_mem, size_t bytes, v
     g.piece_row = reinterpret_cast<const int32_t*>(base + L.piece_row);
     g.piece_beg = reinterpret_cast<const int64_t*>(base + L.piece_beg);
     g.piece_end = reinterpret_cast<const int64_t*>(base + L.piece_end);
+    if (res) {
+      ResPlan& r = g.res;
+      r.on = P.res_on;
+      r.nt = s.res.nt;
+      r.rpt = s.res.rpt;
+      r.nheavy = P.res_nheavy;
+      r.nchunk = static_cast<int32_t>(P.res_hpos.size());
+      for (int v = 0; v < r.nt / 64; ++v)
+        r.quads = std::max(r.quads, P.res_off[(v + 1) * r.rpt] - P.res_off[v * r.rpt]);
+      r.row = reinterpret_cast<const int32_t*>(base + L.res_row);
+      r.pos = reinterpret_cast<const uint16_t*>(base + L.res_pos);
+      r.off = reinterpret_cast<const int32_t*>(base + L.res_off);
+      r.idx = reinterpret_cast<const uint16_t*>(base + L.res_idx);
+      r.w = weighted ? base + L.res_w : nullptr;
+      r.cpos = reinterpret_cast<const uint16_t*>(base + L.res_cpos);
+      r.hpos = reinterpret_cast<const int32_t*>(base + L.res_hpos);
+      r.hbeg = reinterpret_cast<const int32_t*>(base + L.res_hbeg);
+      r.hlen = reinterpret_cast<const int32_t*>(base + L.res_hlen);
+      r.hc0 = reinterpret_cast<const int32_t*>(base + L.res_hc0);
+    }
+    flush();
+    if (res && e == hipSuccess) chk(launch_res_fill(g, h->dt, hs));
+    if (e == hipSuccess) e = hipStreamSynchronize(hs);
+    if (e != hipSuccess) return cleanup(fail(ERC_E_DEVICE, std::string("graph upload: ") + hipGetErrorString(e)));
     *out = h;
     return ERC_OK;
   });
@@ -1099,13 +1336,34 @@ erc_status erc_resistance(erc_handle h, const erc_solve_params* params, void* ws
     hipStream_t s = static_cast<hipStream_t>(stream);
     Work w = carve_work(h, kb, ws_dev, L, (params->flags & ERC_JACOBI) ? 1 : 0);
     if (params->flags & ERC_EARLY_STOP) w.fin2 = 1;
-    st = prepare_work(h, w, L, s);
+    st = prepare_work(w, s);
     if (st != ERC_OK) return st;
     hipEvent_t t0 = h->ev[6], t1 = h->ev[7];
     ERC_HIP(hipEventRecord(t0, s));
     BlockStats bs;
     int blocks = 0;
-    for (int c0 = params->col_begin; c0 < params->col_end; c0 += params->k_block) {
+    // the SpMM timing (ERC_PROFILE_SPMM) has no SpMM to time in the resident CG
+    const bool res = h->dg.res.on && !(params->flags & ERC_PROFILE_SPMM);
+    if (res) {
+      const int step = resident_cols(h, kb);
+      std::vector<int> iters(params->col_end - params->col_begin);
+      for (int c0 = params->col_begin; c0 < params->col_end; c0 += step) {
+        const int nc = std::min(step, params->col_end - c0);
+        const int acc = (c0 == params->col_begin && !(params->flags & ERC_ACCUMULATE)) ? 0 : 1;
+        st = solve_resident(h, params, &w, L, ws_dev, c0, nc, h->m > 0 ? R_dev : nullptr, acc,
+                            iters.data() + (c0 - params->col_begin), &bs, s);
+        if (st != ERC_OK) return st;
+      }
+      // blocks of the caller's width, and the iterations of each, as the block solver counts
+      for (size_t c = 0; c < iters.size(); c += params->k_block) {
+        const auto b = iters.begin() + c;
+        const auto e = iters.begin() + std::min(iters.size(), c + params->k_block);
+        bs.spmm_full += *std::max_element(b, e);
+        ++blocks;
+      }
+      bs.launches = bs.spmm_full;
+    }
+    for (int c0 = res ? params->col_end : params->col_begin; c0 < params->col_end; c0 += params->k_block) {
       const int nc = std::min(params->k_block, params->col_end - c0);
       const int acc = (c0 == params->col_begin && !(params->flags & ERC_ACCUMULATE)) ? 0 : 1;
       st = solve_block(h, params, w, c0, nc, h->m > 0 ? R_dev : nullptr, acc, nullptr, &bs, s);
@@ -1115,12 +1373,10 @@ erc_status erc_resistance(erc_handle h, const erc_solve_params* params, void* ws
     int64_t bad = 0;
     if (h->m > 0) {
       ERC_HIP(launch_count_bad(R_dev, h->m, w, s));
-      double hb = 0.0;
-      ERC_HIP(hipMemcpyAsync(reinterpret_cast<double*>(h->pinned + 2), w.out, 8, hipMemcpyDeviceToHost, s));
+      ERC_HIP(hipMemcpyAsync(h->pinned + 2, w.bad, 8, hipMemcpyDeviceToHost, s));
       ERC_HIP(hipEventRecord(t1, s));
       ERC_HIP(hipStreamSynchronize(s));
-      std::memcpy(&hb, h->pinned + 2, 8);
-      bad = static_cast<int64_t>(hb);
+      std::memcpy(&bad, h->pinned + 2, 8);
     } else {
       ERC_HIP(hipEventRecord(t1, s));
       ERC_HIP(hipStreamSynchronize(s));
@@ -1478,7 +1734,7 @@ erc_status erc_debug_check_plan(const erc_graph_desc* desc) {
     const int64_t n = desc->n;
     const int64_t* rp = desc->rowptr;
     const int64_t nnz = rp[n];
-    const Shape s = make_shape(n, nnz);
+    const Shape s = make_shape(n, nnz, desc->w != nullptr, desc->solve_dtype);
     Plan P;
     build_plan(desc, c, s, &P);
     auto bad = [&](const std::string& what) { return fail(ERC_E_STATE, "plan check: " + what); };
@@ -1529,6 +1785,33 @@ erc_status erc_debug_check_plan(const erc_graph_desc* desc) {
       if (!is_light[i] && rp[i + 1] - rp[i] <= s.heavy) return bad("row in no plan list");
     for (int64_t pos = 0; pos < nnz; ++pos)
       if (cover[pos] != 1) return bad("entry not covered exactly once");
+    // resident CG: a position per row, slots long enough for their rows, and each long row
+    // covered once by its chunks, in order
+    if (!P.res_row.empty()) {
+      if (static_cast<int64_t>(P.res_row.size()) != int64_t{s.res.nt} * s.res.rpt ||
+          static_cast<int64_t>(P.res_row.size()) < n || P.res_off.back() + kResPadQuads > s.quads_max ||
+          static_cast<int64_t>(P.res_hpos.size()) > s.hchunk_max)
+        return bad("resident plan exceeds its size bound");
+      std::vector<unsigned char> seen(n, 0);
+      for (int64_t p = 0; p < n; ++p) {
+        const int64_t i = P.res_row[p];
+        if (i < 0 || i >= n || seen[i]++ || P.res_pos[i] != p) return bad("resident positions");
+        const int64_t dg = rp[i + 1] - rp[i];
+        if ((dg > kResHeavy) != (p < P.res_nheavy)) return bad("resident long rows not first");
+        const int64_t at = (p % s.res.nt) / 64 * s.res.rpt + p / s.res.nt;
+        if (dg <= kResHeavy && 4 * int64_t{P.res_off[at + 1] - P.res_off[at]} < dg)
+          return bad("resident slot shorter than a row");
+      }
+      for (int32_t p = 0; p < P.res_nheavy; ++p) {
+        int64_t next = rp[P.res_row[p]];
+        for (int32_t k = P.res_hc0[p]; k < P.res_hc0[p + 1]; ++k) {
+          if (P.res_hpos[k] != p || P.res_hbeg[k] != next || P.res_hlen[k] < 1 || P.res_hlen[k] > kResChunk)
+            return bad("resident chunk");
+          next += P.res_hlen[k];
+        }
+        if (next != rp[P.res_row[p] + 1]) return bad("resident chunks do not cover their row");
+      }
+    }
     // edge pieces: each upper entry once, edge ids consistent with eid
     std::fill(cover.begin(), cover.end(), 0);
     for (int64_t t = 0; t < np; ++t) {
@@ -1575,7 +1858,7 @@ erc_status erc_debug_rhs(erc_handle h, int32_t K_total, int32_t col0, int32_t nc
     if (static_cast<int64_t>(ws_bytes) < L.total) return fail(ERC_E_WORKSPACE, "workspace too small");
     hipStream_t s = static_cast<hipStream_t>(stream);
     const Work w = carve_work(h, kb, ws_dev, L);
-    erc_status st = prepare_work(h, w, L, s);
+    erc_status st = prepare_work(w, s);
     if (st != ERC_OK) return st;
     ERC_HIP(launch_rhs(h->dg, w, h->dt, K_total, col0, ncols, splitmix_first(seed),
                        1.0 / std::sqrt(static_cast<double>(K_total)), 0.5, s));
@@ -1597,7 +1880,7 @@ erc_status erc_debug_spmm(erc_handle h, double delta, int32_t ncols, const void*
     if (static_cast<int64_t>(ws_bytes) < L.total) return fail(ERC_E_WORKSPACE, "workspace too small");
     hipStream_t s = static_cast<hipStream_t>(stream);
     const Work w = carve_work(h, ncols, ws_dev, L);
-    erc_status st = prepare_work(h, w, L, s);
+    erc_status st = prepare_work(w, s);
     if (st != ERC_OK) return st;
     ERC_HIP(launch_spmm(h->dg, w, h->dt, delta, X_dev, X_dev, Y_dev, w.cs.one, s));
     return ERC_OK;
@@ -1621,12 +1904,15 @@ erc_status erc_debug_solve_block(erc_handle h, const erc_solve_params* params, i
     hipStream_t s = static_cast<hipStream_t>(stream);
     Work w = carve_work(h, kb, ws_dev, L, (params->flags & ERC_JACOBI) ? 1 : 0);
     if (params->flags & ERC_EARLY_STOP) w.fin2 = 1;
-    st = prepare_work(h, w, L, s);
+    st = prepare_work(w, s);
     if (st != ERC_OK) return st;
     BlockStats bs;
-    st = solve_block(h, params, w, col0, ncols, nullptr, 0, iters_host, &bs, s);
+    if (h->dg.res.on && !(params->flags & ERC_PROFILE_SPMM))
+      st = solve_resident(h, params, &w, L, ws_dev, col0, ncols, nullptr, 0, iters_host, &bs, s);
+    else
+      st = solve_block(h, params, w, col0, ncols, nullptr, 0, iters_host, &bs, s);
     if (st != ERC_OK) return st;
-    ERC_HIP(launch_copy_cols(h->dg, w.z, kb, h->dt, ncols, Z_dev, s));
+    ERC_HIP(launch_copy_cols(h->dg, w.z, w.kb, h->dt, ncols, Z_dev, s));
     ERC_HIP(hipStreamSynchronize(s));
     if (bs.breakdowns > 0) return fail(ERC_E_NUMERIC, "CG breakdown");
     if (bs.unconverged > 0) return fail(ERC_E_NOT_CONVERGED, "column(s) reached max_iter");

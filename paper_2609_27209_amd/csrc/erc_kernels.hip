@@ -189,61 +189,10 @@ struct Dot<double> {
 };
 
 // ---------------------------------------------------------------------------------
-// Deterministic grid reduction.  `in` (LDS, nval doubles) holds this block's values.
-// Returns true in exactly one block, with the grid totals in `out` (LDS).  All threads
-// of every block must call it.  Tickets are left at zero for the next launch.
-template <class Op>
-__device__ bool tree_reduce(const Tree& t, int nval, const double* in, double* out) {
-  __shared__ int s_last;
-  const int tid = threadIdx.x;
-  if (gridDim.x == 1) {
-    for (int v = tid; v < nval; v += blockDim.x) out[v] = in[v];
-    __syncthreads();
-    return true;
-  }
-  for (int v = tid; v < nval; v += blockDim.x)
-    t.lvl0[static_cast<size_t>(blockIdx.x) * nval + v] = in[v];
-  int cnt = gridDim.x;
-  int idx = blockIdx.x;
-  const double* src = t.lvl0;
-  uint32_t* tick = t.tick;
-  for (int level = 0;; ++level) {
-    const int ng = (cnt + kTreeFan - 1) / kTreeFan;
-    const int grp = idx / kTreeFan;
-    const int gsize = min(kTreeFan, cnt - grp * kTreeFan);
-    __threadfence();
-    __syncthreads();
-    if (tid == 0) s_last = (atomicAdd(&tick[grp], 1u) == static_cast<unsigned>(gsize - 1));
-    __syncthreads();
-    if (!s_last) return false;
-    __threadfence();
-    double* dst = (ng == 1) ? out : (level == 0 ? t.lvl1 : t.lvl2) + static_cast<size_t>(grp) * nval;
-    for (int v = tid; v < nval; v += blockDim.x) {
-      const double* b = src + static_cast<size_t>(grp) * kTreeFan * nval + v;
-      double s = b[0];
-      for (int k = 1; k < gsize; ++k) s = Op::apply(s, b[static_cast<size_t>(k) * nval]);
-      dst[v] = s;
-    }
-    if (tid == 0) tick[grp] = 0u;
-    if (ng == 1) {
-      __syncthreads();
-      return true;
-    }
-    src = (level == 0) ? t.lvl1 : t.lvl2;
-    tick += ng;
-    cnt = ng;
-    idx = grp;
-  }
-}
-struct OpSum {
-  __device__ static double apply(double a, double b) { return a + b; }
-};
-struct OpMax {
-  __device__ static double apply(double a, double b) { return a > b ? a : b; }
-};
-
-// The same tree for compensated pairs: `in`/`out` are LDS arrays of nval pairs and the
-// level buffers hold nval pairs per block.
+// Deterministic grid reduction of compensated pairs.  `in` (LDS, nval pairs) holds this
+// block's values; the level buffers hold nval pairs per block.  Returns true in exactly one
+// block, with the grid totals in `out` (LDS).  All threads of every block must call it.
+// Tickets are left at zero for the next launch.
 __device__ bool tree_sum_dd(const Tree& t, int nval, const DDv* in, DDv* out) {
   __shared__ int s_last;
   const int tid = threadIdx.x;
@@ -1046,6 +995,7 @@ __global__ __launch_bounds__(kBlock) void k_rhs(RhsArgs a) {
   T* __restrict__ Z = static_cast<T*>(a.z);
   T* __restrict__ R = static_cast<T*>(a.r);
   T* __restrict__ Pp = static_cast<T*>(a.p);
+  const bool state = Z != nullptr;  // else only the right-hand sides are wanted
   const bool aligned = (a.col0 & 63) == 0;
   Dot<T> r0[CPL];
   Dot<T> s0[PC ? CPL : 1];
@@ -1107,6 +1057,7 @@ __global__ __launch_bounds__(kBlock) void k_rhs(RhsArgs a) {
         const T y = (cc < a.ncols) ? static_cast<T>(acc[cl] * a.inv_sqrt_k) : T(0);
         const int64_t o = static_cast<int64_t>(i) * KB + cc;
         R[o] = y;
+        if (!state) continue;
         Z[o] = T(0);
         r0[cl].add(y, y);
         if constexpr (PC) {
@@ -1119,6 +1070,7 @@ __global__ __launch_bounds__(kBlock) void k_rhs(RhsArgs a) {
       }
     }
   }
+  if (!state) return;
 #pragma unroll
   for (int cl = 0; cl < CPL; ++cl) {
     const int cc = cl * 64 + lane;
@@ -1156,6 +1108,7 @@ __global__ __launch_bounds__(kBlock) void k_rhs_unit(RhsArgs a) {
   T* __restrict__ Z = static_cast<T*>(a.z);
   T* __restrict__ R = static_cast<T*>(a.r);
   T* __restrict__ Pp = static_cast<T*>(a.p);
+  const bool state = Z != nullptr;  // else only the right-hand sides are wanted
   const int sh = a.col0 & 63;  // bit of the block's first column in its sign word
   const bool two = sh + KB > 64;
   Dot<T> r0;
@@ -1191,11 +1144,14 @@ __global__ __launch_bounds__(kBlock) void k_rhs_unit(RhsArgs a) {
       const T y = (lane < a.ncols) ? static_cast<T>(static_cast<double>(acc) * a.inv_sqrt_k) : T(0);
       const int64_t o = static_cast<int64_t>(i) * KB + lane;
       R[o] = y;
-      Z[o] = T(0);
-      Pp[o] = y;
-      r0.add(y, y);
+      if (state) {
+        Z[o] = T(0);
+        Pp[o] = y;
+        r0.add(y, y);
+      }
     }
   }
+  if (!state) return;
   if (lane < KB) s_part[wv][lane] = r0.get();
   __syncthreads();
   for (int c = threadIdx.x; c < KB; c += kBlock) {
@@ -1368,29 +1324,32 @@ __global__ __launch_bounds__(kBlock) void k_fill_f64(double* p, double v, int64_
     p[x] = v;
 }
 
-// count of entries that are <= 0 or not finite -> out[0]
+// *bad += the number of entries that are <= 0 or not finite (an integer sum; blocks that
+// find none add nothing)
 __global__ __launch_bounds__(kBlock) void k_count_bad(const double* __restrict__ x, int64_t count,
-                                                      Tree tree, double* out) {
-  __shared__ double s_w[kWavesPerBlock];
-  __shared__ double s_in[1], s_out[1];
-  double c = 0.0;
+                                                      unsigned long long* bad) {
+  int c = 0;
   for (int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; i < count;
        i += static_cast<int64_t>(gridDim.x) * kBlock) {
     const double v = x[i];
-    c += (!(v > 0.0) || !isfinite(v)) ? 1.0 : 0.0;
+    c += (!(v > 0.0) || !isfinite(v)) ? 1 : 0;
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off);
-  if ((threadIdx.x & 63) == 0) s_w[threadIdx.x >> 6] = c;
-  __syncthreads();
+  if ((threadIdx.x & 63) == 0 && c != 0) atomicAdd(bad, static_cast<unsigned long long>(c));
+}
+
+// State that a solve expects: tickets, the finishing step's counter word and the count of
+// bad resistances at zero, the constant gate at one.
+__global__ __launch_bounds__(kBlock) void k_prepare(uint32_t* tick, int nticks,
+                                                    unsigned long long* word,
+                                                    unsigned long long* bad, int32_t* one) {
+  for (int i = threadIdx.x; i < nticks; i += kBlock) tick[i] = 0u;
   if (threadIdx.x == 0) {
-    double s = s_w[0];
-    for (int w = 1; w < kWavesPerBlock; ++w) s += s_w[w];
-    s_in[0] = s;
+    *word = 0ull;
+    *bad = 0ull;
+    *one = 1;
   }
-  __syncthreads();
-  if (!tree_reduce<OpSum>(tree, 1, s_in, s_out)) return;
-  if (threadIdx.x == 0) out[0] = s_out[0];
 }
 
 // dst (n x ncols, row-major) = the first ncols columns of src (n x kb)
@@ -1672,8 +1631,8 @@ static hipError_t rhs_dispatch(erc_dtype dt, int kb, const RhsArgs& a, int grid,
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_rhs(const DevGraph& g, const Work& w, erc_dtype dt, int K, int col0, int ncols,
-                      uint64_t base, double inv_sqrt_k, double tol, hipStream_t s) {
+static RhsArgs rhs_args(const DevGraph& g, const Work& w, int K, int col0, int ncols,
+                        uint64_t base, double inv_sqrt_k) {
   RhsArgs a;
   a.g = g;
   a.z = w.z;
@@ -1686,6 +1645,21 @@ hipError_t launch_rhs(const DevGraph& g, const Work& w, erc_dtype dt, int K, int
   a.inv_sqrt_k = inv_sqrt_k;
   a.part = w.part;
   a.minv = w.pc ? w.minv : nullptr;
+  return a;
+}
+
+hipError_t launch_rhs_only(const DevGraph& g, const Work& w, erc_dtype dt, int K, int col0,
+                           int ncols, uint64_t base, double inv_sqrt_k, hipStream_t s) {
+  RhsArgs a = rhs_args(g, w, K, col0, ncols, base, inv_sqrt_k);
+  a.z = a.p = nullptr;
+  a.part = nullptr;
+  a.minv = nullptr;
+  return rhs_dispatch(dt, w.kb, a, w.grid_rhs, s);
+}
+
+hipError_t launch_rhs(const DevGraph& g, const Work& w, erc_dtype dt, int K, int col0, int ncols,
+                      uint64_t base, double inv_sqrt_k, double tol, hipStream_t s) {
+  const RhsArgs a = rhs_args(g, w, K, col0, ncols, base, inv_sqrt_k);
   hipError_t e = rhs_dispatch(dt, w.kb, a, w.grid_rhs, s);
   if (e != hipSuccess) return e;
   FinArgs f;
@@ -1843,7 +1817,13 @@ hipError_t launch_edge_dist(const DevGraph& g, const Work& w, erc_dtype dt, doub
 
 hipError_t launch_count_bad(const double* x, int64_t count, const Work& w, hipStream_t s) {
   const int grid = grid_for(count, kBlock * 16, 2048);
-  ERC_LAUNCH(k_count_bad, grid, s, x, count, w.tree, w.out);
+  ERC_LAUNCH(k_count_bad, grid, s, x, count, w.bad);
+  return hipGetLastError();
+}
+
+hipError_t launch_prepare(const Work& w, hipStream_t s) {
+  ERC_LAUNCH(k_prepare, 1, s, w.tree.tick, static_cast<int>(tree_ticks(kMaxTreeGrid)), w.cs.fin_word,
+             w.bad, w.cs.one);
   return hipGetLastError();
 }
 

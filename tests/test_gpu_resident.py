@@ -1,0 +1,103 @@
+"""The resident CG (one workgroup per column, small graphs) against the block kernels.
+
+With profile=True (ERC_PROFILE_SPMM) a solve runs the block kernels whatever the graph's
+size, so both paths solve the same right-hand sides.  The sizes sit at the edges of the
+resident plan: one and two rows, a row more or less than a slice (64), than a workgroup (512
+and 1024 threads) and than the largest fp32 and fp64 forms, rows of kResHeavy (128) entries
+and one more, rows of several chunks, isolated rows, and q inside and outside the LDS.
+
+Tolerance: the bars of the parity tests against the oracle, 1e-9 (fp64) and 1e-4 (fp32)
+relative on R; the two paths' rounding differs in the order of row sums and in beta (the
+reduced r.r against its expansion).
+"""
+import numpy as np
+import pytest
+
+import gen
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2609_27209_amd as E
+    return E
+
+
+def _ring(n, weighted, seed, extra=3.0, isolated=0):
+    """A ring on n - isolated nodes with extra * n random chords, ids shuffled."""
+    rng = np.random.default_rng(seed)
+    k = n - isolated
+    u = np.arange(k)
+    v = (u + 1) % k
+    a, b = rng.integers(0, k, int(extra * k)), rng.integers(0, k, int(extra * k))
+    u, v = np.concatenate([u, a]), np.concatenate([v, b])
+    perm = rng.permutation(n)
+    keep = u != v
+    u, v = perm[u[keep]], perm[v[keep]]
+    w = rng.uniform(0.5, 2.0, u.size).astype(np.float32) if weighted else None
+    return gen.from_edges(n, u, v, w)
+
+
+def _hubs(n, degrees, weighted, seed):
+    """A sparse ring plus hubs of the given extra degrees."""
+    rng = np.random.default_rng(seed)
+    us, vs = [np.arange(n)], [(np.arange(n) + 1) % n]
+    for h, d in enumerate(degrees):
+        t = rng.choice(n, d, replace=False)
+        us.append(np.full(d, 7 * h))
+        vs.append(t)
+    u, v = np.concatenate(us), np.concatenate(vs)
+    keep = u != v
+    w = rng.uniform(0.5, 2.0, int(keep.sum())).astype(np.float32) if weighted else None
+    return gen.from_edges(n, u[keep], v[keep], w)
+
+
+CASES = {
+    "two_rows": lambda wt: gen.path_graph(2, None if not wt else np.array([1.5], np.float32)),
+    "n64": lambda wt: _ring(64, wt, 1),
+    "n65_isolated": lambda wt: _ring(65, wt, 2, isolated=9),
+    "n1025": lambda wt: _ring(1025, wt, 3),
+    "n2048": lambda wt: _ring(2048, wt, 4),
+    "n2049": lambda wt: _ring(2049, wt, 5),
+    "long_stream_in_registers": lambda wt: _ring(2000, wt, 6, extra=14.0),
+    "degrees_127_to_129": lambda wt: _hubs(3000, [125, 126, 127, 128, 129], wt, 7),
+    "chunked_rows": lambda wt: _hubs(5000, [255, 256, 257, 513, 4000], wt, 8),
+    "dense": lambda wt: _ring(300, wt, 9, extra=60.0),
+    "n16384": lambda wt: _ring(16384, wt, 10, extra=1.0),
+    "n16385": lambda wt: _ring(16385, wt, 11, extra=1.0),
+    "n32768": lambda wt: _ring(32768, wt, 12, extra=1.0),
+}
+
+
+@pytest.mark.parametrize("precond", ["none", "jacobi"])
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_resident_matches_block_kernels(name, weighted, dtype, precond):
+    E = _gpu()
+    g = CASES[name](weighted)
+    G = E.Graph(g.rowptr, g.col, g.w, solve_dtype=dtype)
+    tol = 1e-6 if dtype == "f32" else 1e-10
+    # 21 columns in blocks of 6 (padded 16 or 8): one resident solve, four ragged blocks
+    a, ia = G.resistance(21, 6, 1e-4, tol, 4000, 5, precond=precond)
+    a = a.cpu().numpy()
+    a2, _ = G.resistance(21, 6, 1e-4, tol, 4000, 5, precond=precond)
+    np.testing.assert_array_equal(a2.cpu().numpy(), a)
+    b, ib = G.resistance(21, 6, 1e-4, tol, 4000, 5, precond=precond, profile=True)
+    b = b.cpu().numpy()
+    assert ia["blocks"] == ib["blocks"] == 4
+    assert ia["cols_unconverged"] == ib["cols_unconverged"] == 0
+    assert np.max(np.abs(a - b) / b) <= (1e-9 if dtype == "f64" else 1e-4)
+
+
+def test_resident_iteration_cap_is_reported():
+    E = _gpu()
+    g = _ring(3000, True, 21)
+    G = E.Graph(g.rowptr, g.col, g.w, solve_dtype="f32")
+    _, i3 = G.resistance(16, 16, 1e-4, 1e-6, 3, 5, raise_not_converged=False)
+    assert i3["iters_max"] == 3 and i3["iters_total"] == 48 and i3["cols_unconverged"] == 16
+    assert i3["max_final_relres"] > 1e-6
