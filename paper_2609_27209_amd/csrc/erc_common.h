@@ -233,20 +233,29 @@ constexpr uint32_t kDrawBadProb = 1u;      // a probability outside [0, 1] or Na
 constexpr uint32_t kDrawSumTooLarge = 2u;  // probabilities sum above 1.5
 constexpr uint32_t kDrawAllZero = 4u;      // every integer weight is zero
 constexpr uint32_t kSubBadIndex = 8u;      // a drawn index outside the node or edge range
-constexpr int64_t kScanTile = 4096;        // items per block of the prefix-sum kernels
+constexpr int64_t kScanTile = 4096;        // items per block of a scan
+constexpr int64_t kBitTile = 1024;         // bitmap words per block
+constexpr int64_t kDrawSub = 16;           // items of a subtile of a draw's weights
 inline int64_t scan_blocks(int64_t items) { return ceil_div(items, kScanTile); }
+// Words of a bitmap over `items`, in whole tiles of at least one.
+inline int64_t sub_words(int64_t items) {
+  return kBitTile * (items > 0 ? ceil_div(items, 32 * kBitTile) : 1);
+}
 
 struct DrawWork {
-  uint64_t* cdf;     // N+1: exclusive prefix sums of the integer weights, cdf[N] = total
-  uint64_t* bsum;    // scan_blocks(N) block sums
-  double* psum;      // scan_blocks(N) fp64 block sums of the probabilities
-  uint32_t* status;  // one word, zero before the launch
+  uint64_t* sub;     // scan_blocks(N) x kScanTile / kDrawSub: prefix sums within each tile
+  uint64_t* tsum;    // scan_blocks(N) + 1: tile sums, then their prefix sums and the total
+  double* psum;      // scan_blocks(N) fp64 tile sums of the probabilities
+  uint32_t* status;  // one word
 };
 struct SubgraphWork {
-  uint32_t* npos;    // n+1: node flags, then their exclusive prefix sums (new ids)
-  uint32_t* epos;    // m+1: edge flags, then their exclusive prefix sums
-  uint32_t* bsum;    // scan_blocks(max(n, m)) block sums
-  uint32_t* status;  // one word, zero before the launch
+  uint32_t* head;       // status, kept nodes, kept edges (followed by the bitmaps)
+  uint32_t* nbits;      // bitmap of the kept nodes
+  uint32_t* ebits;      // bitmap of the kept edges (edge draws)
+  int64_t clear_words;  // words from head that a call starts from zero
+  uint32_t* nprefix;    // rank of each node word's first bit
+  uint32_t* cnt;        // up to n: edges per kept node, then their prefix sums (node draws)
+  uint32_t* tile;       // tile sums
 };
 hipError_t launch_draw(const double* prob, int64_t N, int64_t draws, uint64_t base,
                        const DrawWork& w, int64_t* idx, hipStream_t s);

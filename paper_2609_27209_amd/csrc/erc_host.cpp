@@ -643,6 +643,8 @@ constexpr int kPinnedInts = 4096;
 // pinned slot (8-byte aligned) of the sampling call's non-finite-curvature flag, past the
 // per-column readback of the widest block (8 + 4 * 256 + 4 * 256 ints)
 constexpr int kPinSampleFlag = 4064;
+// pinned slot of the draw and subgraph calls' status and counts
+constexpr int kPinDraw = 4072;
 
 WorkLayout work_layout(const erc_graph_s* h, int kb) {
   WorkLayout L{};
@@ -1547,7 +1549,7 @@ erc_status erc_sampling_probs_static(erc_handle h, const double* kappa_dev, doub
 
 namespace {
 struct DrawLayout {
-  int64_t cdf, bsum, psum, status, total;
+  int64_t sub, tsum, psum, status, total;
 };
 DrawLayout draw_layout(int64_t N) {
   DrawLayout L{};
@@ -1558,15 +1560,16 @@ DrawLayout draw_layout(int64_t N) {
     return at;
   };
   const int64_t nb = std::max<int64_t>(1, scan_blocks(N));
-  L.cdf = take((N + 1) * 8);
-  L.bsum = take(nb * 8);
+  L.sub = take(nb * (kScanTile / kDrawSub) * 8);
+  L.tsum = take((nb + 1) * 8);
   L.psum = take(nb * 8);
   L.status = take(4);
   L.total = off;
   return L;
 }
+constexpr int64_t kSubAlign = 16;
 struct SubLayout {
-  int64_t npos, epos, bsum, status, total;
+  int64_t head, nbits, ebits, nprefix, cnt, tile, total;
 };
 SubLayout sub_layout(const erc_graph_s* h) {
   SubLayout L{};
@@ -1576,16 +1579,23 @@ SubLayout sub_layout(const erc_graph_s* h) {
     off = align_up(off + std::max<int64_t>(bytes, 0), 256);
     return at;
   };
-  L.npos = take((h->n + 1) * 4);
-  L.epos = take((h->m + 1) * 4);
-  L.bsum = take(std::max<int64_t>(1, scan_blocks(std::max(h->n, h->m))) * 4);
-  L.status = take(4);
-  L.total = off;
+  L.head = take(16);
+  L.nbits = take(sub_words(h->n) * 4);
+  L.ebits = take(sub_words(h->m) * 4);
+  L.nprefix = take(sub_words(h->n) * 4);
+  L.cnt = take(h->n * 4);
+  L.tile = take(std::max({sub_words(h->n) / kBitTile, sub_words(h->m) / kBitTile, scan_blocks(h->n)}) * 4);
+  L.total = off + kSubAlign;  // the bitmaps are read 16 bytes at a time
+
   return L;
 }
-erc_status read_status(uint32_t* status_dev, hipStream_t s, uint32_t* out) {
-  ERC_HIP(hipMemcpyAsync(out, status_dev, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+// `words` device words to the handle's pinned slot, waited for: a copy to pageable memory
+// would be staged by the runtime.
+erc_status read_words(erc_graph_s* h, const uint32_t* src, int words, hipStream_t s, const uint32_t** out) {
+  uint32_t* slot = reinterpret_cast<uint32_t*>(h->pinned + kPinDraw);
+  ERC_HIP(hipMemcpyAsync(slot, src, static_cast<size_t>(words) * 4, hipMemcpyDeviceToHost, s));
   ERC_HIP(hipStreamSynchronize(s));
+  *out = slot;
   return ERC_OK;
 }
 }  // namespace
@@ -1618,16 +1628,16 @@ erc_status erc_draw(erc_handle h, erc_items items, const double* prob_dev, int64
       return fail(ERC_E_WORKSPACE, "scratch smaller than erc_draw_scratch_bytes");
     char* b = static_cast<char*>(scratch_dev);
     DrawWork w{};
-    w.cdf = reinterpret_cast<uint64_t*>(b + L.cdf);
-    w.bsum = reinterpret_cast<uint64_t*>(b + L.bsum);
+    w.sub = reinterpret_cast<uint64_t*>(b + L.sub);
+    w.tsum = reinterpret_cast<uint64_t*>(b + L.tsum);
     w.psum = reinterpret_cast<double*>(b + L.psum);
     w.status = reinterpret_cast<uint32_t*>(b + L.status);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    ERC_HIP(launch_fill_u32(w.status, 0u, 1, s));
     ERC_HIP(launch_draw(prob_dev, N, draws, splitmix_first(seed), w, idx_dev, s));
-    uint32_t st = 0;
-    erc_status rs = read_status(w.status, s, &st);
+    const uint32_t* back = nullptr;
+    erc_status rs = read_words(h, w.status, 1, s, &back);
     if (rs != ERC_OK) return rs;
+    const uint32_t st = back[0];
     if (st & kDrawBadProb) return fail(ERC_E_NUMERIC, "a probability is NaN or outside [0, 1]");
     if (st & kDrawSumTooLarge) return fail(ERC_E_NUMERIC, "probabilities sum above 1.5");
     if (st & kDrawAllZero) return fail(ERC_E_NUMERIC, "every probability rounds to a zero weight");
@@ -1663,25 +1673,27 @@ erc_status erc_subgraph(erc_handle h, erc_items items, const int64_t* idx_dev, i
     const SubLayout L = sub_layout(h);
     if (static_cast<int64_t>(scratch_bytes) < L.total)
       return fail(ERC_E_WORKSPACE, "scratch smaller than erc_subgraph_scratch_bytes");
-    char* b = static_cast<char*>(scratch_dev);
+    char* b = static_cast<char*>(scratch_dev) +
+              (-reinterpret_cast<uintptr_t>(scratch_dev) & static_cast<uintptr_t>(kSubAlign - 1));
     SubgraphWork w{};
-    w.npos = reinterpret_cast<uint32_t*>(b + L.npos);
-    w.epos = reinterpret_cast<uint32_t*>(b + L.epos);
-    w.bsum = reinterpret_cast<uint32_t*>(b + L.bsum);
-    w.status = reinterpret_cast<uint32_t*>(b + L.status);
+    w.head = reinterpret_cast<uint32_t*>(b + L.head);
+    w.nbits = reinterpret_cast<uint32_t*>(b + L.nbits);
+    w.ebits = reinterpret_cast<uint32_t*>(b + L.ebits);
+    // node draws keep no edge bitmap
+    w.clear_words = ((items == ERC_NODES ? L.ebits : L.nprefix) - L.head) / 4;
+    w.nprefix = reinterpret_cast<uint32_t*>(b + L.nprefix);
+    w.cnt = reinterpret_cast<uint32_t*>(b + L.cnt);
+    w.tile = reinterpret_cast<uint32_t*>(b + L.tile);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    ERC_HIP(launch_fill_u32(w.status, 0u, 1, s));
     ERC_HIP(launch_subgraph(h->dg, items == ERC_NODES ? 0 : 1, idx_dev, count, w, nodes_dev,
                             edges_dev, u_dev, v_dev, s));
-    uint32_t tot[2] = {0u, 0u};
-    ERC_HIP(hipMemcpyAsync(&tot[0], w.npos + h->n, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-    ERC_HIP(hipMemcpyAsync(&tot[1], w.epos + h->m, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-    uint32_t st = 0;
-    erc_status rs = read_status(w.status, s, &st);
+    const uint32_t* back = nullptr;
+    erc_status rs = read_words(h, w.head, 3, s, &back);
     if (rs != ERC_OK) return rs;
+    const uint32_t st = back[0];
     if (st & kSubBadIndex) return fail(ERC_E_INVALID_ARG, "a drawn index is out of range");
-    counts_host[0] = tot[0];
-    counts_host[1] = tot[1];
+    counts_host[0] = back[1];
+    counts_host[1] = back[2];
     return ERC_OK;
   });
 }
