@@ -174,7 +174,7 @@ erc_status erc_validate(const erc_graph_desc* desc, int64_t* m_out);
 erc_status erc_graph_bytes(const erc_graph_desc* desc, size_t* bytes);
 
 /* Validate and canonicalise the graph on the host, then copy the device copy of the
- * operator (CSR, weights, per-entry edge ids, sqrt(w) per edge, work lists) into
+ * operator (CSR, weights, per-entry edge ids, endpoints and sqrt(w) per edge, work lists) into
  * dev_mem (device, >= erc_graph_bytes bytes, 256-byte aligned) on `stream`, and wait
  * for the copy.  The handle refers to dev_mem, which must stay allocated until
  * erc_destroy.  (Algorithm 1: construct sparse L; store local sparse operators.) */
@@ -318,9 +318,10 @@ erc_status erc_probe_gather_sliced(const int32_t* idx_dev, int64_t count, const 
 /* ---- test hooks (same conventions; used by the parity tests) ---------------------- */
 
 /* Host-only self-check of the work plan erc_create would build for this graph (no GPU
- * needed): every stored entry is covered exactly once by the SpMM plan, every upper
- * entry (v > u) exactly once by the per-edge pieces, every index is in range and every
- * list fits the size bounds behind erc_graph_bytes.  ERC_E_STATE names a violation. */
+ * needed): every stored entry is covered exactly once by the SpMM plan, and where the
+ * graph has one by the plan of the single-launch solve, the upper entries (v > u) carry the
+ * canonical edge ids in order, every index is in range and every list fits the size bounds
+ * behind erc_graph_bytes.  ERC_E_STATE names a violation. */
 erc_status erc_debug_check_plan(const erc_graph_desc* desc);
 
 /* Canonical edge id of every stored CSR entry (device, nnz int32). */

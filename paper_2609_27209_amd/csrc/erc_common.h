@@ -95,11 +95,10 @@ struct DevGraph {
   const int32_t* mega_chunk0;  // first chunk slot of each multi-chunk row
   int32_t nchunk_slots;
 
-  // Edge pieces: ranges of the upper (v > u) entries of one row, for per-edge kernels
-  int64_t npiece;
-  const int32_t* piece_row;
-  const int64_t* piece_beg;  // CSR position
-  const int64_t* piece_end;
+  // Endpoints u < v of every edge, in canonical order: the per-edge kernels run over edges
+  // rather than rows, whose upper parts are short and uneven
+  const int32_t* eu;  // m
+  const int32_t* ev;  // m
 
   ResPlan res;
 };
@@ -179,6 +178,7 @@ hipError_t launch_node_p(const DevGraph& g, erc_dtype dt, const double* R, doubl
                          hipStream_t s);
 hipError_t launch_edge_kappa(const DevGraph& g, const double* R, const double* p, double* kappa,
                              hipStream_t s);
+// u[e], v[e] from the CSR arrays (erc_create fills eu and ev with it)
 hipError_t launch_endpoints(const DevGraph& g, int32_t* u, int32_t* v, hipStream_t s);
 hipError_t launch_eids(const DevGraph& g, int32_t* out, hipStream_t s);
 

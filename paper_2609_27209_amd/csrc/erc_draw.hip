@@ -451,8 +451,7 @@ __global__ __launch_bounds__(kBlock) void k_emit_edges(DevGraph g, const uint32_
   }
 }
 
-// Endpoints of the kept edges (old numbering) and their bits: u is the last row with
-// ubase[u] <= e, which then has an upper entry for e.
+// Endpoints of the kept edges (old numbering) and their bits.
 __global__ __launch_bounds__(kBlock) void k_endpoints_of(DevGraph g, const int64_t* __restrict__ edges,
                                                          const uint32_t* __restrict__ mkept,
                                                          int32_t* __restrict__ uo,
@@ -462,13 +461,7 @@ __global__ __launch_bounds__(kBlock) void k_endpoints_of(DevGraph g, const int64
   const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
   for (int64_t k = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; k < m; k += stride) {
     const int64_t e = edges[k];
-    int lo = 0, hi = g.n;  // ubase[lo] <= e < ubase[hi]
-    while (hi - lo > 1) {
-      const int mid = lo + ((hi - lo) >> 1);
-      if (g.ubase[mid] <= e) lo = mid;
-      else hi = mid;
-    }
-    const int32_t v = g.col[g.rowptr[lo + 1] - (g.ubase[lo + 1] - e)];
+    const int32_t lo = g.eu[e], v = g.ev[e];
     uo[k] = lo;
     vo[k] = v;
     // edges run by u: one of a run of equal u marks it

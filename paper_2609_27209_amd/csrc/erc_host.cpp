@@ -67,8 +67,6 @@ constexpr int kMaxSpmmGrid = 16384;
 constexpr int64_t kRowsPerWave = 32;
 static_assert((kMaxSpmmGrid + kTreeFan - 1) / kTreeFan <= kMaxTreeGrid,
               "level-1 sums of the SpMM partials must fit the tree buffers");
-// Longest edge piece of the per-edge kernels.
-constexpr int64_t kPiece = 1024;
 // Grid caps of the other kernels.
 constexpr int kMaxGridRhs = 8192;
 // The update streams seven n x kb arrays; 32768 blocks (about 4.6 vectors per thread
@@ -114,7 +112,7 @@ struct Shape {
   int waves, grid;   // SpMM wavefronts and blocks
   int64_t heavy;     // rows with degree above this are block tasks
   int64_t chunk;     // block tasks are at most this long
-  int64_t ntask_max, nmega_max, nslot_max, npiece_max;
+  int64_t ntask_max, nmega_max, nslot_max;
   ResForm res;       // form of the resident CG (0 slots: the graph is too large for it)
   int64_t quads_max, hchunk_max;
 };
@@ -143,7 +141,6 @@ Shape make_shape(int64_t n, int64_t nnz, bool weighted, erc_dtype dt) {
   s.ntask_max = nnz / s.heavy + nnz / s.chunk + 1;
   s.nmega_max = nnz / s.chunk + 1;
   s.nslot_max = 2 * (nnz / s.chunk) + 1;
-  s.npiece_max = n + s.m / kPiece + 1;
   if (nnz * (2 + (weighted ? static_cast<int64_t>(dsize(dt)) : 0)) <= kResMaxStream) s.res = res_form(dt, n);
   if (s.res.rpt > 0) {
     // rows run by decreasing degree, so 64 x (longest row) summed over the wavefronts' slots
@@ -157,7 +154,7 @@ Shape make_shape(int64_t n, int64_t nnz, bool weighted, erc_dtype dt) {
 // Byte layout of the graph buffer.
 struct GraphLayout {
   int64_t rowptr, col, w, eid, sw, ubase, deg, light, wave_lo, task_row, task_mega, task_chunk,
-      task_beg, task_end, mega_row, mega_nchunk, mega_chunk0, piece_row, piece_beg, piece_end,
+      task_beg, task_end, mega_row, mega_nchunk, mega_chunk0, eu, ev,
       res_row, res_pos, res_off, res_idx, res_w, res_cpos, res_hpos, res_hbeg, res_hlen, res_hc0,
       total;
 };
@@ -187,9 +184,6 @@ GraphLayout graph_layout(const Shape& s, bool weighted, erc_dtype dt) {
   L.mega_row = take(s.nmega_max * 4);
   L.mega_nchunk = take(s.nmega_max * 4);
   L.mega_chunk0 = take(s.nmega_max * 4);
-  L.piece_row = take(s.npiece_max * 4);
-  L.piece_beg = take(s.npiece_max * 8);
-  L.piece_end = take(s.npiece_max * 8);
   if (s.res.rpt > 0) {
     const int64_t sz = static_cast<int64_t>(dsize(dt));
     L.res_row = take(int64_t{s.res.nt} * s.res.rpt * 4);
@@ -203,6 +197,8 @@ GraphLayout graph_layout(const Shape& s, bool weighted, erc_dtype dt) {
     L.res_w = take(weighted ? s.quads_max * 256 * sz : 0);
     L.res_cpos = take(s.nnz * 2);
   }
+  L.eu = take(s.m * 4);
+  L.ev = take(s.m * 4);
   L.total = off;
   return L;
 }
@@ -410,8 +406,6 @@ struct Plan {
   std::vector<int64_t> task_beg, task_end;
   std::vector<int32_t> mega_row, mega_nchunk, mega_chunk0;
   int32_t nslot = 0;
-  std::vector<int32_t> piece_row;
-  std::vector<int64_t> piece_beg, piece_end;
   // resident CG (empty if the graph has no such plan)
   std::vector<int32_t> res_row, res_off, res_hpos, res_hbeg, res_hlen, res_hc0;
   std::vector<uint16_t> res_pos;
@@ -509,7 +503,7 @@ void build_res_plan(const erc_graph_desc* d, const Shape& s, Plan* P) {
   if (P->res_on == 0) P->res_row.clear();
 }
 
-void build_plan(const erc_graph_desc* d, const Canon& c, const Shape& s, Plan* P) {
+void build_plan(const erc_graph_desc* d, const Shape& s, Plan* P) {
   const int64_t n = d->n;
   const int64_t* rp = d->rowptr;
   // long rows -> block tasks, longest first; very long rows are split into chunks
@@ -583,16 +577,6 @@ void build_plan(const erc_graph_desc* d, const Canon& c, const Shape& s, Plan* P
   }
   while (w < W - 1) P->wave_lo[++w] = static_cast<int32_t>(nl);
   P->wave_lo[W] = static_cast<int32_t>(nl);
-  // edge pieces over the upper entries of each row
-  for (int64_t u = 0; u < n; ++u) {
-    const int64_t up = c.ubase[u + 1] - c.ubase[u];
-    const int64_t upos = rp[u + 1] - up;
-    for (int64_t b = upos; b < rp[u + 1]; b += kPiece) {
-      P->piece_row.push_back(static_cast<int32_t>(u));
-      P->piece_beg.push_back(b);
-      P->piece_end.push_back(std::min(rp[u + 1], b + kPiece));
-    }
-  }
   if (s.res.rpt > 0) build_res_plan(d, s, P);
 }
 
@@ -653,7 +637,7 @@ WorkLayout work_layout(const erc_graph_s* h, int kb) {
   L.grid_rhs = static_cast<int>(std::min<int64_t>(kMaxGridRhs, std::max<int64_t>(1, ceil_div(h->n, kWavesPerBlock))));
   const int64_t nvec = h->n * kb / vec;
   L.grid_upd = static_cast<int>(std::min<int64_t>(kMaxGridUpd, std::max<int64_t>(1, ceil_div(nvec, kBlock * 4))));
-  L.grid_ed = static_cast<int>(std::min<int64_t>(kMaxGridEd, std::max<int64_t>(1, ceil_div(h->dg.npiece, kWavesPerBlock))));
+  L.grid_ed = static_cast<int>(std::min<int64_t>(kMaxGridEd, std::max<int64_t>(1, ceil_div(h->m, 64 * kWavesPerBlock))));
   L.grid_tree = std::max({h->dg.grid, L.grid_rhs, L.grid_upd});
   int64_t off = 0;
   auto take = [&](int64_t bytes) {
@@ -1077,10 +1061,10 @@ erc_status erc_create(const erc_graph_desc* desc, void* dev_mem, size_t bytes, v
     if (static_cast<int64_t>(bytes) < L.total)
       return fail(ERC_E_WORKSPACE, "graph buffer smaller than erc_graph_bytes");
     Plan P;
-    build_plan(desc, c, s, &P);
+    build_plan(desc, s, &P);
     if (static_cast<int64_t>(P.task_row.size()) > s.ntask_max ||
         static_cast<int64_t>(P.mega_nchunk.size()) > s.nmega_max ||
-        static_cast<int64_t>(P.piece_row.size()) > s.npiece_max || P.nslot > s.nslot_max ||
+        P.nslot > s.nslot_max ||
         (!P.res_row.empty() && (P.res_off.back() + kResPadQuads > s.quads_max ||
                                 static_cast<int64_t>(P.res_hpos.size()) > s.hchunk_max)))
       return fail(ERC_E_STATE, "internal: work plan exceeds its size bound");
@@ -1189,10 +1173,6 @@ erc_status erc_create(const erc_graph_desc* desc, void* dev_mem, size_t bytes, v
     chk(up(L.mega_row, P.mega_row.data(), nm * 4));
     chk(up(L.mega_nchunk, P.mega_nchunk.data(), nm * 4));
     chk(up(L.mega_chunk0, P.mega_chunk0.data(), nm * 4));
-    const int64_t np = static_cast<int64_t>(P.piece_row.size());
-    chk(up(L.piece_row, P.piece_row.data(), np * 4));
-    chk(up(L.piece_beg, P.piece_beg.data(), np * 8));
-    chk(up(L.piece_end, P.piece_end.data(), np * 8));
     const bool res = !P.res_row.empty();
     if (res) {
       chk(up(L.res_row, P.res_row.data(), static_cast<int64_t>(P.res_row.size()) * 4));
@@ -1231,10 +1211,8 @@ erc_status erc_create(const erc_graph_desc* desc, void* dev_mem, size_t bytes, v
     g.mega_nchunk = reinterpret_cast<const int32_t*>(base + L.mega_nchunk);
     g.mega_chunk0 = reinterpret_cast<const int32_t*>(base + L.mega_chunk0);
     g.nchunk_slots = P.nslot;
-    g.npiece = np;
-    g.piece_row = reinterpret_cast<const int32_t*>(base + L.piece_row);
-    g.piece_beg = reinterpret_cast<const int64_t*>(base + L.piece_beg);
-    g.piece_end = reinterpret_cast<const int64_t*>(base + L.piece_end);
+    g.eu = reinterpret_cast<const int32_t*>(base + L.eu);
+    g.ev = reinterpret_cast<const int32_t*>(base + L.ev);
     if (res) {
       ResPlan& r = g.res;
       r.on = P.res_on;
@@ -1256,6 +1234,8 @@ erc_status erc_create(const erc_graph_desc* desc, void* dev_mem, size_t bytes, v
       r.hc0 = reinterpret_cast<const int32_t*>(base + L.res_hc0);
     }
     flush();
+    if (e == hipSuccess)
+      chk(launch_endpoints(g, const_cast<int32_t*>(g.eu), const_cast<int32_t*>(g.ev), hs));
     if (res && e == hipSuccess) chk(launch_res_fill(g, h->dt, hs));
     if (e == hipSuccess) e = hipStreamSynchronize(hs);
     if (e != hipSuccess) return cleanup(fail(ERC_E_DEVICE, std::string("graph upload: ") + hipGetErrorString(e)));
@@ -1289,7 +1269,12 @@ erc_status erc_edge_endpoints(erc_handle h, int32_t* u_dev, int32_t* v_dev, void
     g_last_error.clear();
     if (check_handle(h) != ERC_OK) return ERC_E_INVALID_ARG;
     if (h->m > 0 && (u_dev == nullptr || v_dev == nullptr)) return fail(ERC_E_INVALID_ARG, "output is NULL");
-    ERC_HIP(launch_endpoints(h->dg, u_dev, v_dev, static_cast<hipStream_t>(stream)));
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    const size_t bytes = static_cast<size_t>(h->m) * sizeof(int32_t);
+    if (bytes > 0) {
+      ERC_HIP(hipMemcpyAsync(u_dev, h->dg.eu, bytes, hipMemcpyDeviceToDevice, s));
+      ERC_HIP(hipMemcpyAsync(v_dev, h->dg.ev, bytes, hipMemcpyDeviceToDevice, s));
+    }
     return ERC_OK;
   });
 }
@@ -1748,12 +1733,11 @@ erc_status erc_debug_check_plan(const erc_graph_desc* desc) {
     const int64_t nnz = rp[n];
     const Shape s = make_shape(n, nnz, desc->w != nullptr, desc->solve_dtype);
     Plan P;
-    build_plan(desc, c, s, &P);
+    build_plan(desc, s, &P);
     auto bad = [&](const std::string& what) { return fail(ERC_E_STATE, "plan check: " + what); };
     const int64_t nt = static_cast<int64_t>(P.task_row.size());
     const int64_t nm = static_cast<int64_t>(P.mega_nchunk.size());
-    const int64_t np = static_cast<int64_t>(P.piece_row.size());
-    if (nt > s.ntask_max || nm > s.nmega_max || np > s.npiece_max || P.nslot > s.nslot_max)
+    if (nt > s.ntask_max || nm > s.nmega_max || P.nslot > s.nslot_max)
       return bad("list exceeds its size bound");
     if (s.grid < 1 || s.grid > kMaxSpmmGrid || s.waves != s.grid * kWavesPerBlock)
       return bad("grid shape");
@@ -1824,25 +1808,15 @@ erc_status erc_debug_check_plan(const erc_graph_desc* desc) {
         if (next != rp[P.res_row[p] + 1]) return bad("resident chunks do not cover their row");
       }
     }
-    // edge pieces: each upper entry once, edge ids consistent with eid
-    std::fill(cover.begin(), cover.end(), 0);
-    for (int64_t t = 0; t < np; ++t) {
-      const int64_t u = P.piece_row[t];
-      if (u < 0 || u >= n) return bad("piece row out of range");
+    // the upper entries follow the lower ones in each row and are numbered in order
+    for (int64_t u = 0; u < n; ++u) {
       const int64_t up = c.ubase[u + 1] - c.ubase[u];
-      const int64_t upos = rp[u + 1] - up;
-      if (P.piece_beg[t] < upos || P.piece_end[t] > rp[u + 1] || P.piece_beg[t] >= P.piece_end[t])
-        return bad("piece outside the upper entries of its row");
-      for (int64_t pos = P.piece_beg[t]; pos < P.piece_end[t]; ++pos) {
-        if (desc->col[pos] <= u) return bad("piece covers a lower entry");
-        const int64_t e = c.ubase[u] + (pos - upos);
-        if (e != c.eid[pos]) return bad("piece edge id differs from the entry's edge id");
-        cover[pos] += 1;
+      for (int64_t pos = rp[u]; pos < rp[u + 1]; ++pos) {
+        const bool upper = pos >= rp[u + 1] - up;
+        if ((desc->col[pos] > u) != upper) return bad("upper entries are not the row's last");
+        if (upper && c.eid[pos] != c.ubase[u] + (pos - (rp[u + 1] - up))) return bad("edge id of an upper entry");
       }
     }
-    for (int64_t u = 0; u < n; ++u)
-      for (int64_t pos = rp[u]; pos < rp[u + 1]; ++pos)
-        if ((desc->col[pos] > u) != (cover[pos] == 1)) return bad("upper entry not covered exactly once");
     return ERC_OK;
   });
 }

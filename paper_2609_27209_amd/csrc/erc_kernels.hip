@@ -1204,59 +1204,75 @@ __global__ __launch_bounds__(kBlock) void k_fin_rhs(FinArgs a) {
   }
 }
 
-// R_e (+)= sum_c (z_uc - z_vc)^2 over the upper entries (v > u) of each piece.  The
-// squared difference is formed in fp64; LPN lanes sum one edge's columns.
+// Sum over each aligned group of LPN lanes, in every lane of the group: DPP exchanges within
+// 16 lanes (a mirror pairs lanes that already hold equal sums), shuffles beyond.
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double x) {
+  const long long b = __double_as_longlong(x);
+  const int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(b), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(b >> 32), CTRL, 0xf, 0xf, true);
+  return __longlong_as_double((static_cast<long long>(hi) << 32) | static_cast<unsigned>(lo));
+}
+template <int LPN>
+__device__ __forceinline__ double group_sum(double d) {
+  if (LPN >= 2) d += dpp_f64<0xB1>(d);    // lanes xor 1
+  if (LPN >= 4) d += dpp_f64<0x4E>(d);    // lanes xor 2
+  if (LPN >= 8) d += dpp_f64<0x141>(d);   // the other four of eight
+  if (LPN >= 16) d += dpp_f64<0x140>(d);  // the other eight of sixteen
+  if (LPN >= 32) d += __shfl_xor(d, 16);
+  if (LPN >= 64) d += __shfl_xor(d, 32);
+  return d;
+}
+
+// R_e (+)= sum_c (z_uc - z_vc)^2, 64 edges at a time per wavefront.  The squared difference is
+// formed in fp64; LPN lanes sum one edge's columns.  Step st handles the NPW = 64 / LPN edges
+// grp * LPN + st (grp the lane group), so that the lane with sub == st keeps the sum of the
+// edge it loaded and R is read and written in order.  Consecutive edges share u, whose row
+// then comes from the L1.  What bounds it: the gathers of z beyond the L2.  A wavefront per
+// row part took 3.69 ms per 64 columns of the 62M-edge workload (18.6 GB), half of it on the
+// chains of loads that start a short row; over the edge list it takes 2.40 (20,000 nodes:
+// 22 -> 6 us).
 template <typename T, int LPN>
 __global__ __launch_bounds__(kBlock) void k_edge_dist(DevGraph g, const T* __restrict__ Z,
                                                       double* __restrict__ R, int accumulate) {
   constexpr int VEC = V<T>::N;
   constexpr int KB = LPN * VEC;
-  constexpr int NPW = 64 / LPN;
+  constexpr int NI = LPN >= 8 ? 8 : 4;  // steps in flight, two rows each
+  static_assert(LPN % NI == 0, "steps come in groups of NI");
   const int lane = threadIdx.x & 63;
-  const int grp = lane / LPN;
   const int sub = lane % LPN;
-  const int64_t nw = static_cast<int64_t>(gridDim.x) * kWavesPerBlock;
-  for (int64_t t = static_cast<int64_t>(blockIdx.x) * kWavesPerBlock + (threadIdx.x >> 6);
-       t < g.npiece; t += nw) {
-    const int u = g.piece_row[t];
-    const int64_t pb = g.piece_beg[t];
-    const int64_t pe = g.piece_end[t];
-    const int64_t upos = g.rowptr[u + 1] - (g.ubase[u + 1] - g.ubase[u]);
-    const int64_t ebase = g.ubase[u] + (pb - upos);
-    const V<T> zu = ldv(Z + static_cast<int64_t>(u) * KB + sub * VEC);
-    for (int64_t base = pb; base < pe; base += 64) {
-      const int cnt = static_cast<int>(min(static_cast<int64_t>(64), pe - base));
-      const int64_t e0 = ebase + (base - pb);
-      // this window's neighbours and (when accumulating) their previous R, one
-      // coalesced load each; then kInflight neighbour rows of z in flight per lane
-      const int myj = (lane < cnt) ? g.col[base + lane] : u;
-      const double myr = (accumulate && lane < cnt) ? R[e0 + lane] : 0.0;
-      const int steps = (cnt + NPW - 1) / NPW;
-      for (int st0 = 0; st0 < steps; st0 += kInflight) {
-        V<T> zv[kInflight];
+  const int g0 = lane - sub;
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
+  for (int64_t e0 = static_cast<int64_t>(blockIdx.x) * kBlock + (threadIdx.x - lane); e0 < g.m; e0 += stride) {
+    const int64_t e = e0 + lane;
+    const bool in = e < g.m;
+    const int myu = g.eu[in ? e : g.m - 1];
+    const int myv = g.ev[in ? e : g.m - 1];
+    const double prev = accumulate && in ? R[e] : 0.0;
+    double mine = 0.0;
+#pragma unroll 1
+    for (int s0 = 0; s0 < LPN; s0 += NI) {
+      V<T> zu[NI], zv[NI];
 #pragma unroll
-        for (int q = 0; q < kInflight; ++q) {
-          const int k = (st0 + q) * NPW + grp;
-          int j = __shfl(myj, k & 63);
-          if (k >= cnt) j = u;
-          zv[q] = ldv(Z + static_cast<int64_t>(j) * KB + sub * VEC);
+      for (int q = 0; q < NI; ++q) {
+        const int u = __shfl(myu, g0 + s0 + q);
+        const int v = __shfl(myv, g0 + s0 + q);
+        zu[q] = ldv(Z + static_cast<int64_t>(u) * KB + sub * VEC);
+        zv[q] = ldv(Z + static_cast<int64_t>(v) * KB + sub * VEC);
+      }
+#pragma unroll
+      for (int q = 0; q < NI; ++q) {
+        double d = 0.0;
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) {
+          const double df = static_cast<double>(zu[q].x[v]) - static_cast<double>(zv[q].x[v]);
+          d += df * df;
         }
-#pragma unroll
-        for (int q = 0; q < kInflight; ++q) {
-          const int k = (st0 + q) * NPW + grp;
-          double d = 0.0;
-#pragma unroll
-          for (int v = 0; v < VEC; ++v) {
-            const double df = static_cast<double>(zu.x[v]) - static_cast<double>(zv[q].x[v]);
-            d += df * df;
-          }
-#pragma unroll
-          for (int off = 1; off < LPN; off <<= 1) d += __shfl_xor(d, off);
-          const double r0 = __shfl(myr, k & 63);
-          if (sub == 0 && k < cnt) R[e0 + k] = accumulate ? r0 + d : d;
-        }
+        d = group_sum<LPN>(d);
+        if (sub == s0 + q) mine = d;
       }
     }
+    if (in) R[e] = accumulate ? prev + mine : mine;
   }
 }
 
@@ -1280,40 +1296,27 @@ __global__ __launch_bounds__(kBlock) void k_node_p(DevGraph g, const double* __r
   }
 }
 
-// kappa_e = 2 (p_u + p_v) / R_e over the edge pieces, one lane per edge.
+// kappa_e = 2 (p_u + p_v) / R_e, one thread per edge (62M edges: 1.22 ms over the rows' parts,
+// 1.00 over the edge list).
 __global__ __launch_bounds__(kBlock) void k_edge_kappa(DevGraph g, const double* __restrict__ R,
                                                        const double* __restrict__ p,
                                                        double* __restrict__ kappa) {
-  const int lane = threadIdx.x & 63;
-  const int64_t nw = static_cast<int64_t>(gridDim.x) * kWavesPerBlock;
-  for (int64_t t = static_cast<int64_t>(blockIdx.x) * kWavesPerBlock + (threadIdx.x >> 6);
-       t < g.npiece; t += nw) {
-    const int u = g.piece_row[t];
-    const int64_t pb = g.piece_beg[t], pe = g.piece_end[t];
-    const int64_t upos = g.rowptr[u + 1] - (g.ubase[u + 1] - g.ubase[u]);
-    const int64_t ebase = g.ubase[u] + (pb - upos);
-    const double pu = p[u];
-    for (int64_t pos = pb + lane; pos < pe; pos += 64) {
-      const int64_t e = ebase + (pos - pb);
-      kappa[e] = 2.0 * (pu + p[g.col[pos]]) / R[e];
-    }
-  }
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
+  for (int64_t e = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; e < g.m; e += stride)
+    kappa[e] = 2.0 * (p[g.eu[e]] + p[g.ev[e]]) / R[e];
 }
 
+// Endpoints of every edge: the upper entries of each row in order, one wavefront per row.
 __global__ __launch_bounds__(kBlock) void k_endpoints(DevGraph g, int32_t* __restrict__ eu,
                                                       int32_t* __restrict__ ev) {
   const int lane = threadIdx.x & 63;
-  const int64_t nw = static_cast<int64_t>(gridDim.x) * kWavesPerBlock;
-  for (int64_t t = static_cast<int64_t>(blockIdx.x) * kWavesPerBlock + (threadIdx.x >> 6);
-       t < g.npiece; t += nw) {
-    const int u = g.piece_row[t];
-    const int64_t pb = g.piece_beg[t], pe = g.piece_end[t];
-    const int64_t upos = g.rowptr[u + 1] - (g.ubase[u + 1] - g.ubase[u]);
-    const int64_t ebase = g.ubase[u] + (pb - upos);
-    for (int64_t pos = pb + lane; pos < pe; pos += 64) {
-      const int64_t e = ebase + (pos - pb);
-      eu[e] = u;
-      ev[e] = g.col[pos];
+  const int nw = gridDim.x * kWavesPerBlock;
+  for (int i = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6); i < g.n; i += nw) {
+    const int64_t e0 = g.ubase[i], cnt = g.ubase[i + 1] - e0;
+    const int64_t beg = g.rowptr[i + 1] - cnt;
+    for (int64_t k = lane; k < cnt; k += 64) {
+      eu[e0 + k] = i;
+      ev[e0 + k] = g.col[beg + k];
     }
   }
 }
@@ -1797,7 +1800,7 @@ static hipError_t ed_launch(const DevGraph& g, const void* z, double* R, int acc
 
 hipError_t launch_edge_dist(const DevGraph& g, const Work& w, erc_dtype dt, double* R,
                             int accumulate, hipStream_t s) {
-  if (g.npiece == 0) return hipSuccess;
+  if (g.m == 0) return hipSuccess;
   const int lpn = (dt == ERC_F32) ? w.kb / 4 : w.kb / 2;
   const int grid = w.grid_ed;
   if (dt == ERC_F32) {
@@ -1858,16 +1861,14 @@ hipError_t launch_node_p(const DevGraph& g, erc_dtype dt, const double* R, doubl
 
 hipError_t launch_edge_kappa(const DevGraph& g, const double* R, const double* p, double* kappa,
                              hipStream_t s) {
-  if (g.npiece == 0) return hipSuccess;
-  const int grid = grid_for(g.npiece, kWavesPerBlock, 8192);
-  ERC_LAUNCH(k_edge_kappa, grid, s, g, R, p, kappa);
+  if (g.m == 0) return hipSuccess;
+  ERC_LAUNCH(k_edge_kappa, grid_for(g.m, kBlock * 4, 16384), s, g, R, p, kappa);
   return hipGetLastError();
 }
 
 hipError_t launch_endpoints(const DevGraph& g, int32_t* u, int32_t* v, hipStream_t s) {
-  if (g.npiece == 0) return hipSuccess;
-  const int grid = grid_for(g.npiece, kWavesPerBlock, 8192);
-  ERC_LAUNCH(k_endpoints, grid, s, g, u, v);
+  if (g.m == 0) return hipSuccess;
+  ERC_LAUNCH(k_endpoints, grid_for(g.n, kWavesPerBlock, 8192), s, g, u, v);
   return hipGetLastError();
 }
 
