@@ -603,6 +603,7 @@ struct erc_graph_s {
   bool weighted = false;
   int device = 0;
   int64_t nonisolated = 0;
+  int64_t max_degree = 0;
   Shape shape{};
   DevGraph dg{};
   int32_t* pinned = nullptr;  // host poll slots and per-column readback
@@ -982,6 +983,19 @@ erc_status solve_resident(erc_graph_s* h, const erc_solve_params* p, Work* w, co
   return ERC_OK;
 }
 
+// Whether a solve takes the resident CG.  Not with ERC_PROFILE_SPMM, whose timing has no SpMM
+// launch there; and in fp64 without preconditioning only if no row has more than 32 entries:
+// up to there both solvers sum a row's terms in the same order and give the same bits.  On a
+// 1970-node power-law graph, whose hubs are summed in another order, a few hundred iterations
+// amplify that to 9e-9 of kappa (either is 7e-9 to 8e-9 from the exact solution of the system),
+// where a caller of the fp64 path may look for 1e-9.  The Jacobi variant's few iterations keep
+// such differences to 6e-10 and below.
+constexpr int64_t kResSameOrder = 32;  // rows that the SpMM's lane groups sum one entry after the other
+bool takes_resident(const erc_graph_s* h, const erc_solve_params* p) {
+  if (!h->dg.res.on || (p->flags & ERC_PROFILE_SPMM)) return false;
+  return h->dt == ERC_F32 || (p->flags & ERC_JACOBI) || h->max_degree <= kResSameOrder;
+}
+
 // Columns that one resident solve takes: as many as the workspace's four n x kb arrays hold
 // (once, or twice where q is in memory too) and the widest edge-distance kernel reads.
 int resident_cols(const erc_graph_s* h, int kb) {
@@ -1100,7 +1114,10 @@ erc_status erc_create(const erc_graph_desc* desc, void* dev_mem, size_t bytes, v
     h->dt = desc->solve_dtype;
     h->weighted = weighted;
     h->shape = s;
-    for (int64_t i = 0; i < n; ++i) h->nonisolated += desc->rowptr[i + 1] > desc->rowptr[i];
+    for (int64_t i = 0; i < n; ++i) {
+      h->nonisolated += desc->rowptr[i + 1] > desc->rowptr[i];
+      h->max_degree = std::max(h->max_degree, desc->rowptr[i + 1] - desc->rowptr[i]);
+    }
     auto cleanup = [&](erc_status e) {
       if (h->pinned) (void)hipHostFree(h->pinned);
       for (auto& ev : h->ev)
@@ -1329,8 +1346,7 @@ erc_status erc_resistance(erc_handle h, const erc_solve_params* params, void* ws
     ERC_HIP(hipEventRecord(t0, s));
     BlockStats bs;
     int blocks = 0;
-    // the SpMM timing (ERC_PROFILE_SPMM) has no SpMM to time in the resident CG
-    const bool res = h->dg.res.on && !(params->flags & ERC_PROFILE_SPMM);
+    const bool res = takes_resident(h, params);
     if (res) {
       const int step = resident_cols(h, kb);
       std::vector<int> iters(params->col_end - params->col_begin);
@@ -1893,7 +1909,7 @@ erc_status erc_debug_solve_block(erc_handle h, const erc_solve_params* params, i
     st = prepare_work(w, s);
     if (st != ERC_OK) return st;
     BlockStats bs;
-    if (h->dg.res.on && !(params->flags & ERC_PROFILE_SPMM))
+    if (takes_resident(h, params))
       st = solve_resident(h, params, &w, L, ws_dev, col0, ncols, nullptr, 0, iters_host, &bs, s);
     else
       st = solve_block(h, params, w, col0, ncols, nullptr, 0, iters_host, &bs, s);

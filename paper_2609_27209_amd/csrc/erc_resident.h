@@ -8,18 +8,21 @@
 // launch, grid-wide reduction or host poll sits between iterations.
 //
 // What bounds it: on the smallest graphs the chain of reductions, barriers and LDS round
-// trips of an iteration (2000 rows: 3.1 us in fp32, 3.8 us in fp64), on larger ones the LDS
+// trips of an iteration (2000 rows: 3.1 us in fp32, 5.2 us in fp64), on larger ones the LDS
 // gathers, whose random banks collide (64-lane gathers take 7 cycles instead of 2), and the
 // vector instructions around them (20,000 rows, 220,000 entries: 20.6 us; LDS busy 61% of
 // the time, over half of it conflicts, vector units 49%), with the operator's stream from the
 // L2 (2 bytes of position and the weight per entry) behind them.  The block kernels took 28,
 // 28 and 54 us for these iterations of 32, 64 and 64 columns, as three or four dependent
-// launches each.  Whole steps: 2000 rows fp64 1.19 -> 0.29 ms, 2000 rows and 1024 columns
+// launches each.  Whole steps: 2000 rows fp64 1.19 -> 0.35 ms, 2000 rows and 1024 columns
 // 16.5 -> 0.70 ms, 20,000 rows 1.95 -> 0.92 ms, 12,305 rows fp64 Jacobi 4.8 -> 1.2 ms.
 //
 // The recurrence is Hestenes-Stiefel CG with the stopping rule and the precision of the
 // block kernels: fp32 or fp64 vectors, inner products in fp64 or double-double, rows above
-// kResHeavy entries summed in fp64; beta uses the reduced r.r of the updated residual.
+// kResHeavy entries summed in fp64.  In fp64 beta also has their expanded form, so that rows
+// which both sum one entry after the other give the same bits from both (fp64 CG is where a
+// caller looks for agreement beyond the stopping tolerance, and a few ten iterations amplify
+// the last bit of a beta to 1e-8 of the solution); fp32 takes r.r of the stored r.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -49,7 +52,7 @@ hipError_t res_solve_f64(const ResArgs& a, int ncols, size_t lds, hipStream_t s)
 // rows: there an iteration is mostly reductions, whose instructions every wavefront of a SIMD
 // issues in turn, against the latency that more wavefronts hide (2000 rows, 38 iterations of
 // fp32 and 42 of fp64, us per solve with 256 / 512 / 1024 threads: 205 / 142 / 163 and
-// 227 / 173 / 196).
+// 227 / 173 / 196, the latter with one inner product less than now).
 inline constexpr ResForm kForms32[] = {{512, 2}, {512, 4}, {1024, 4}, {1024, 6}, {1024, 8}, {1024, 12},
                                        {1024, 16}, {1024, 20}, {1024, 24}, {1024, 28}, {1024, 32}};
 inline constexpr ResForm kForms64[] = {{512, 2}, {512, 4}, {1024, 4}, {1024, 6}, {1024, 8},
@@ -108,6 +111,15 @@ struct Acc<double> {
     return DD{t, a.c + (e + pe)};
   }
   __device__ __forceinline__ static double value(V a) { return a.s + a.c; }
+  __device__ __forceinline__ static V times(V a, double b) {
+#pragma clang fp contract(off)
+    const double p = a.s * b;
+    const double pe = fma(a.s, b, -p);
+    const double c = pe + a.c * b;
+    V r;
+    two_sum(p, c, r.s, r.c);
+    return r;
+  }
 };
 
 // Lane exchanges within 16-lane rows by DPP (a few cycles each, against an LDS round trip
@@ -265,17 +277,17 @@ __global__ __launch_bounds__(NT) void k_resident(ResArgs a) {
   const int ends = a.p.off[wv * RPT + min(lane + 1, RPT)];
 
   // sums over the workgroup of K values at once, in every thread; partial set b is free
-  // again when the barrier after the next has passed
+  // again when the barrier after the next has passed (set 0: up to three sums, set 1: one)
   auto block_sums = [&](AV* x, auto kk, int b) {
     constexpr int K = decltype(kk)::value;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       const AV t = wave_sum<A>(x[k]);
-      if (lane == 0) s_red[2 * b + k][wv] = t;
+      if (lane == 0) s_red[3 * b + k][wv] = t;
     }
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < K; ++k) x[k] = row_sum<A>((lane & 15) < NW ? s_red[2 * b + k][lane & (NW - 1)] : A::zero());
+    for (int k = 0; k < K; ++k) x[k] = row_sum<A>((lane & 15) < NW ? s_red[3 * b + k][lane & (NW - 1)] : A::zero());
   };
   static_assert(NW <= 16, "row_sum adds 16 partials");
 
@@ -289,7 +301,10 @@ __global__ __launch_bounds__(NT) void k_resident(ResArgs a) {
   }
 
   T z[RPT], r[RPT];
-  AV dot[2] = {A::zero(), A::zero()};
+  // r.r, then r.M^-1 r with the Jacobi variant, or r.q and q.q of the expanded beta
+  constexpr bool X = sizeof(T) == 8 && !PC;
+  constexpr int ND = X ? 3 : PC ? 2 : 1;
+  AV dot[3] = {A::zero(), A::zero(), A::zero()};
 #pragma unroll
   for (int s = 0; s < RPT; ++s) {
     const int pos = s * NT + tid;
@@ -426,20 +441,24 @@ __global__ __launch_bounds__(NT) void k_resident(ResArgs a) {
       const T al = static_cast<T>(rho / pqv);
       Global<const T> mv = fresh(static_cast<const T*>(a.minv));
       const Global<const T> gq = fresh(static_cast<const T*>(a.q)) + static_cast<int64_t>(c) * a.n;
-      dot[0] = dot[1] = A::zero();
+      dot[0] = dot[1] = dot[2] = A::zero();
 #pragma unroll
       for (int s = 0; s < RPT; ++s) {
         const int pos = s * NT + tid;
         T q = T(0);
         if (pos < a.n) q = QL ? s_q[pos] : gq[pos];
         z[s] += al * s_p[pos];
+        if constexpr (X) {
+          dot[1] = here(A::mac(dot[1], r[s], q));
+          dot[2] = here(A::mac(dot[2], q, q));
+        }
         r[s] -= al * q;
         dot[0] = A::mac(dot[0], r[s], r[s]);
+        if constexpr (X) dot[0] = here(dot[0]);
         if constexpr (PC) dot[1] = here(A::mac(dot[1], r[s], mv[pos] * r[s]));
-        if (s % 8 == 7) asm volatile("" ::: "memory");
+        if (s % (X ? 2 : 8) == (X ? 1 : 7)) asm volatile("" ::: "memory");
       }
-      if constexpr (PC) block_sums(dot, Count<2>(), 0);
-      else block_sums(dot, Count<1>(), 0);
+      block_sums(dot, Count<ND>(), 0);
       rr = A::value(dot[0]);
       const double rs = PC ? A::value(dot[1]) : rr;
       ++iters;
@@ -452,7 +471,13 @@ __global__ __launch_bounds__(NT) void k_resident(ResArgs a) {
       }
       // 4. p = r + beta p (p = M^-1 r + beta p; an explicit fma, so that both variants round
       // alike); unused after the last iteration
-      const T be = static_cast<T>(rs / rho);
+      double rn = rs;
+      if constexpr (X) {
+        const double a1 = rho / pqv;
+        const AV t = A::add(A::add(AV{rho, 0.0}, A::times(dot[1], -2.0 * a1)), A::times(A::times(dot[2], a1), a1));
+        rn = A::value(t) > 0.0 ? A::value(t) : 0.0;
+      }
+      const T be = static_cast<T>(rn / rho);
       rho = rs;
       mv = fresh(static_cast<const T*>(a.minv));
       tid = fresh_lane(tid);
