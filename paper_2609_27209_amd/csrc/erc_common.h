@@ -202,9 +202,10 @@ hipError_t launch_resident(const DevGraph& g, erc_dtype dt, void* y, void* q, in
 struct SampleWork {
   double* part_mm;   // grid x 3 block partials (-kappa_min, kappa_max, non-finite flag),
                      // then grid edge-weight block sums
-  double* part_n;    // up to grid node-weight block sums
+  double* part_n;    // grid_n node-weight block sums
   double* totals;    // [0] -kappa_min, [1] kappa_max, [2] node sum, [3] edge sum, [4] bad flag
-  int32_t grid;
+  int32_t grid;      // blocks of the per-edge passes
+  int32_t grid_n;    // blocks of the per-node pass, a multiple of eight
 };
 hipError_t launch_sampling(const DevGraph& g, const double* kappa, double eta, int64_t nonisolated,
                            const SampleWork& sw, double* pn, double* pe, hipStream_t s);

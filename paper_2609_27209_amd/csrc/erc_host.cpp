@@ -77,10 +77,12 @@ constexpr int kMaxGridUpd = 32768;
 static_assert((kMaxGridUpd + kTreeFan - 1) / kTreeFan <= kMaxTreeGrid,
               "level-1 sums of the update partials must fit the tree buffers");
 constexpr int kMaxGridEd = 8192;
-// Grid cap of the sampling passes: their scratch is 4 doubles per block plus 64 bytes,
-// 33 KB at the cap, inside the fixed scratch of erc_sampling_probs_static.
+// Grid caps of the sampling passes: their scratch is 3 doubles per edge block, one per node
+// block and 64 bytes, 41 KB at the caps, inside the fixed scratch of
+// erc_sampling_probs_static.
 constexpr int kSampleGrid = 1024;
-static_assert(int64_t{kSampleGrid} * 4 * 8 + 3 * 256 <= static_cast<int64_t>(kStaticScratchBytes),
+constexpr int kSampleGridN = 2048;
+static_assert(int64_t{kSampleGrid} * 3 * 8 + int64_t{kSampleGridN} * 8 + 3 * 256 <= static_cast<int64_t>(kStaticScratchBytes),
               "the sampling scratch at the grid cap must fit the fixed scratch");
 // Largest operator stream (position and weight bytes per column and iteration) and number of
 // long-row chunks of the resident CG.  A workgroup streams the operator from the L2 by itself
@@ -1446,16 +1448,13 @@ erc_status erc_curvature(erc_handle h, const double* R_dev, double* p_dev, doubl
 namespace {
 struct SampleLayout {
   int64_t part_mm, part_n, totals, total;
-  int grid;
+  int grid, grid_n;
 };
 SampleLayout sample_layout(const erc_graph_s* h) {
   SampleLayout L{};
-  // eight items per thread for the per-edge passes, and at least one block per 32 rows
-  // for the per-node pass (a wavefront per row: on small graphs a grid sized by items
-  // alone left each wavefront a long chain of dependent row loads)
-  const int64_t items = std::max(h->n, h->m);
-  const int64_t want = std::max(ceil_div(items, kBlock * 8), ceil_div(h->n, kWavesPerBlock * 8));
-  L.grid = static_cast<int>(std::min<int64_t>(kSampleGrid, std::max<int64_t>(1, want)));
+  // eight items per thread for the per-edge passes; a block per 16 rows for the per-node pass
+  L.grid = static_cast<int>(std::min<int64_t>(kSampleGrid, std::max<int64_t>(1, ceil_div(std::max(h->n, h->m), kBlock * 8))));
+  L.grid_n = static_cast<int>(std::min<int64_t>(kSampleGridN, align_up(ceil_div(h->n, kWavesPerBlock * 4), 8)));
   int64_t off = 0;
   auto take = [&](int64_t bytes) {
     const int64_t at = off;
@@ -1463,7 +1462,7 @@ SampleLayout sample_layout(const erc_graph_s* h) {
     return at;
   };
   L.part_mm = take(static_cast<int64_t>(L.grid) * 3 * 8);
-  L.part_n = take(static_cast<int64_t>(L.grid) * 8);
+  L.part_n = take(static_cast<int64_t>(L.grid_n) * 8);
   L.totals = take(8 * 8);
   L.total = off;
   return L;
@@ -1500,6 +1499,7 @@ erc_status sampling_probs_into(erc_graph_s* h, const double* kappa_dev, double e
   sw.part_n = reinterpret_cast<double*>(b + L.part_n);
   sw.totals = reinterpret_cast<double*>(b + L.totals);
   sw.grid = L.grid;
+  sw.grid_n = L.grid_n;
   // every partial and total is written before it is read, in stream order: nothing is
   // cleared and no ticket is kept between calls
   ERC_HIP(launch_sampling(h->dg, kappa_dev, eta, h->nonisolated, sw, node_prob_dev, edge_prob_dev, s));
