@@ -15,8 +15,6 @@ constexpr int kBlock = 256;
 constexpr int kWavesPerBlock = kBlock / 64;
 // Fan-in of one level of the deterministic grid reduction tree.
 constexpr int kTreeFan = 32;
-// Largest grid of a kernel whose block partials are reduced by a finishing launch.
-constexpr int kMaxGrid = 8192;
 // Largest grid of a launch that reduces through the ticket tree directly.
 constexpr int kMaxTreeGrid = 2048;
 
@@ -154,7 +152,6 @@ struct Work {
 
 // Launchers (erc_kernels.hip).  All return hipSuccess or the launch error.
 hipError_t launch_fill_u32(uint32_t* p, uint32_t v, int64_t count, hipStream_t s);
-hipError_t launch_fill_f64(double* p, double v, int64_t count, hipStream_t s);
 hipError_t launch_rhs(const DevGraph& g, const Work& w, erc_dtype dt, int K, int col0, int ncols,
                       uint64_t base, double inv_sqrt_k, double tol, hipStream_t s);
 // the right-hand sides alone, into w.r (no CG state)

@@ -673,7 +673,7 @@ WorkLayout work_layout(const erc_graph_s* h, int kb) {
   const int64_t nval = 10 * kb;  // up to five compensated (s, c) pairs per column
   L.part = take(static_cast<int64_t>(L.grid_tree) * 6 * kb * 8);
   L.part_u = take(static_cast<int64_t>(L.grid_upd) * 4 * kb * 8);  // r.r and r.M^-1 r
-  // the finishing launches run ceil(grid/32) <= 256 blocks; k_count_bad runs <= 2048
+  // the finishing launches leave ceil(grid/32) <= 1024 level-1 sums
   L.lvl0 = take(static_cast<int64_t>(kMaxTreeGrid) * nval * 8);
   L.lvl1 = take(ceil_div(kMaxTreeGrid, kTreeFan) * nval * 8);
   L.lvl2 = take(ceil_div(kMaxTreeGrid, kTreeFan * kTreeFan) * nval * 8);

@@ -6,8 +6,10 @@
 //                (Eq. 5; the matrix-free operator of Section 3.1.3).
 //   k_update     z += alpha p, r -= alpha q, p = r + beta p, and r.r (column-wise CG,
 //                Section 3.1.3; Algorithm 1).
-//   k_edge_dist  R_e += sum_c (z_uc - z_vc)^2 (Eq. 6; Algorithm 1, edge blocks).
+//   k_edge_dist  R_e += sum_c (z_uc - z_vc)^2 (Eq. 6; Algorithm 1, edge blocks), over the
+//                list of edge endpoints that k_endpoints writes at creation.
 //   k_node_p, k_edge_kappa   node and edge curvature (Eq. 2).
+//   (Small graphs' CG runs in erc_resident.h instead of k_spmm and k_update.)
 //   k_minmax, k_node_w, k_edge_w, k_normalise   sampling probabilities (Eqs. 7, 8).
 //
 // Layout: every n x kb block (z, r, p, q) is row-major with kb a power of two, so one
@@ -15,9 +17,9 @@
 // 16-byte load each and a wavefront covers NPW = 64 / LPN neighbours per instruction.
 //
 // Determinism: no floating-point atomics anywhere.  Each block reduces its partial
-// sums in a fixed order and the grid combines block partials through a fixed-fan-in
-// tree (tree_sum): an integer ticket only elects which block performs each level, the
-// summation order is a function of the grid size alone.  Results are therefore
+// sums in a fixed order, and the next launch (or, for the right-hand sides, a fixed-fan-in
+// tree, tree_sum_dd, whose integer tickets only elect which block performs each level) combines
+// the block partials: the summation order is a function of the grid size alone.  Results are therefore
 // bit-identical from run to run.
 #include <hip/hip_runtime.h>
 
@@ -1373,12 +1375,6 @@ __global__ __launch_bounds__(kBlock) void k_fill_u32(uint32_t* p, uint32_t v, in
        x += static_cast<int64_t>(gridDim.x) * kBlock)
     p[x] = v;
 }
-__global__ __launch_bounds__(kBlock) void k_fill_f64(double* p, double v, int64_t count) {
-  for (int64_t x = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; x < count;
-       x += static_cast<int64_t>(gridDim.x) * kBlock)
-    p[x] = v;
-}
-
 // *bad += the number of entries that are <= 0 or not finite (an integer sum; blocks that
 // find none add nothing)
 __global__ __launch_bounds__(kBlock) void k_count_bad(const double* __restrict__ x, int64_t count,
@@ -1581,12 +1577,6 @@ hipError_t launch_fill_u32(uint32_t* p, uint32_t v, int64_t count, hipStream_t s
   ERC_LAUNCH(k_fill_u32, grid_for(count, kBlock, 4096), s, p, v, count);
   return hipGetLastError();
 }
-hipError_t launch_fill_f64(double* p, double v, int64_t count, hipStream_t s) {
-  if (count <= 0) return hipSuccess;
-  ERC_LAUNCH(k_fill_f64, grid_for(count, kBlock, 4096), s, p, v, count);
-  return hipGetLastError();
-}
-
 template <int KB>
 static hipError_t fin_rhs_launch(const FinArgs& f, hipStream_t s) {
   ERC_LAUNCH((k_fin_rhs<KB>), (f.nparts + kTreeFan - 1) / kTreeFan, s, f);
