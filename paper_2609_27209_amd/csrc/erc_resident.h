@@ -59,6 +59,8 @@ inline constexpr ResForm kForms64[] = {{512, 2}, {512, 4}, {1024, 4}, {1024, 6},
                                        {1024, 10}, {1024, 13}, {1024, 16}};
 // Quads that a wavefront of a 512-thread form can keep in registers for the whole solve.
 constexpr int kResRegQuads = 16;
+// Sums of a workgroup that the LDS has room for: four of an update and p.q.
+constexpr int kResSums = 5;
 
 // Places for q that a form's kernels exist for: beside p in the LDS (a form's last rows may be
 // missing, which leaves room), and outside it.
@@ -263,7 +265,7 @@ __global__ __launch_bounds__(NT) void k_resident(ResArgs a) {
   __shared__ T s_p[RPT * NT];
   extern __shared__ __attribute__((aligned(16))) char smem[];
   AV (*s_red)[NW] = reinterpret_cast<AV (*)[NW]>(smem);
-  double* s_h = reinterpret_cast<double*>(&s_red[4][0]);
+  double* s_h = reinterpret_cast<double*>(&s_red[kResSums][0]);
   T* s_q = reinterpret_cast<T*>(s_h + ((a.p.nchunk + 1) & ~1));
 
   int tid = threadIdx.x;
@@ -277,17 +279,17 @@ __global__ __launch_bounds__(NT) void k_resident(ResArgs a) {
   const int ends = a.p.off[wv * RPT + min(lane + 1, RPT)];
 
   // sums over the workgroup of K values at once, in every thread; partial set b is free
-  // again when the barrier after the next has passed (set 0: up to three sums, set 1: one)
+  // again when the barrier after the next has passed (set 0: up to four sums, set 1: one)
   auto block_sums = [&](AV* x, auto kk, int b) {
     constexpr int K = decltype(kk)::value;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       const AV t = wave_sum<A>(x[k]);
-      if (lane == 0) s_red[3 * b + k][wv] = t;
+      if (lane == 0) s_red[4 * b + k][wv] = t;
     }
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < K; ++k) x[k] = row_sum<A>((lane & 15) < NW ? s_red[3 * b + k][lane & (NW - 1)] : A::zero());
+    for (int k = 0; k < K; ++k) x[k] = row_sum<A>((lane & 15) < NW ? s_red[4 * b + k][lane & (NW - 1)] : A::zero());
   };
   static_assert(NW <= 16, "row_sum adds 16 partials");
 
@@ -301,10 +303,12 @@ __global__ __launch_bounds__(NT) void k_resident(ResArgs a) {
   }
 
   T z[RPT], r[RPT];
-  // r.r, then r.M^-1 r with the Jacobi variant, or r.q and q.q of the expanded beta
-  constexpr bool X = sizeof(T) == 8 && !PC;
-  constexpr int ND = X ? 3 : PC ? 2 : 1;
-  AV dot[3] = {A::zero(), A::zero(), A::zero()};
+  // r.r, then r.M^-1 r with the Jacobi variant, then r.q and q.q of the expanded beta
+  // (weighted by M^-1 with the Jacobi variant)
+  constexpr bool X = sizeof(T) == 8;
+  constexpr int R = PC ? 2 : 1;
+  constexpr int ND = X ? R + 2 : R;
+  AV dot[4] = {A::zero(), A::zero(), A::zero(), A::zero()};
 #pragma unroll
   for (int s = 0; s < RPT; ++s) {
     const int pos = s * NT + tid;
@@ -441,7 +445,7 @@ __global__ __launch_bounds__(NT) void k_resident(ResArgs a) {
       const T al = static_cast<T>(rho / pqv);
       Global<const T> mv = fresh(static_cast<const T*>(a.minv));
       const Global<const T> gq = fresh(static_cast<const T*>(a.q)) + static_cast<int64_t>(c) * a.n;
-      dot[0] = dot[1] = dot[2] = A::zero();
+      dot[0] = dot[1] = dot[2] = dot[3] = A::zero();
 #pragma unroll
       for (int s = 0; s < RPT; ++s) {
         const int pos = s * NT + tid;
@@ -449,8 +453,9 @@ __global__ __launch_bounds__(NT) void k_resident(ResArgs a) {
         if (pos < a.n) q = QL ? s_q[pos] : gq[pos];
         z[s] += al * s_p[pos];
         if constexpr (X) {
-          dot[1] = here(A::mac(dot[1], r[s], q));
-          dot[2] = here(A::mac(dot[2], q, q));
+          const T m = PC ? mv[pos] : T(1);
+          dot[R] = here(A::mac(dot[R], PC ? r[s] * m : r[s], q));
+          dot[R + 1] = here(A::mac(dot[R + 1], PC ? q * m : q, q));
         }
         r[s] -= al * q;
         dot[0] = A::mac(dot[0], r[s], r[s]);
@@ -474,7 +479,7 @@ __global__ __launch_bounds__(NT) void k_resident(ResArgs a) {
       double rn = rs;
       if constexpr (X) {
         const double a1 = rho / pqv;
-        const AV t = A::add(A::add(AV{rho, 0.0}, A::times(dot[1], -2.0 * a1)), A::times(A::times(dot[2], a1), a1));
+        const AV t = A::add(A::add(AV{rho, 0.0}, A::times(dot[R], -2.0 * a1)), A::times(A::times(dot[R + 1], a1), a1));
         rn = A::value(t) > 0.0 ? A::value(t) : 0.0;
       }
       const T be = static_cast<T>(rn / rho);
