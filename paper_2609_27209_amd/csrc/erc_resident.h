@@ -15,7 +15,7 @@
 // L2 (2 bytes of position and the weight per entry) behind them.  The block kernels took 28,
 // 28 and 54 us for these iterations of 32, 64 and 64 columns, as three or four dependent
 // launches each.  Whole steps: 2000 rows fp64 1.19 -> 0.35 ms, 2000 rows and 1024 columns
-// 16.5 -> 0.70 ms, 20,000 rows 1.95 -> 0.92 ms, 12,305 rows fp64 Jacobi 4.8 -> 1.2 ms.
+// 16.5 -> 0.70 ms, 20,000 rows 1.95 -> 0.92 ms, 12,305 rows fp64 Jacobi 4.8 -> 1.3 ms.
 //
 // The recurrence is Hestenes-Stiefel CG with the stopping rule and the precision of the
 // block kernels: fp32 or fp64 vectors, inner products in fp64 or double-double, rows above
