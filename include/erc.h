@@ -321,8 +321,9 @@ erc_status erc_probe_gather_sliced(const int32_t* idx_dev, int64_t count, const 
 /* Host-only self-check of the work plan erc_create would build for this graph (no GPU
  * needed): every stored entry is covered exactly once by the SpMM plan, and where the
  * graph has one by the plan of the single-launch solve, the upper entries (v > u) carry the
- * canonical edge ids in order, every index is in range and every list fits the size bounds
- * behind erc_graph_bytes.  ERC_E_STATE names a violation. */
+ * canonical edge ids in order, every index is in range, every list fits the size bounds
+ * behind erc_graph_bytes, and the copies of erc_create bring every array to its place.
+ * ERC_E_STATE names a violation. */
 erc_status erc_debug_check_plan(const erc_graph_desc* desc);
 
 /* Canonical edge id of every stored CSR entry (device, nnz int32). */

@@ -582,6 +582,129 @@ void build_plan(const erc_graph_desc* d, const Shape& s, Plan* P) {
   if (s.res.rpt > 0) build_res_plan(d, s, P);
 }
 
+// One array of the graph buffer that erc_create fills from host memory.
+struct HostArray {
+  int64_t off;
+  const void* src;
+  int64_t bytes;
+};
+// One copy to the device: of `stage` if it holds anything, else straight from src.
+struct UploadCopy {
+  int64_t off;
+  const void* src;
+  int64_t bytes;
+  std::vector<char> stage;
+  const void* data() const { return stage.empty() ? src : stage.data(); }
+};
+// Everything that erc_create copies to the device, with the host arrays made for it alone.
+struct Upload {
+  std::vector<float> wf;  // weights in the working precision, where it is not the input's
+  std::vector<double> wd;
+  std::vector<LightRow> light;
+  std::vector<HostArray> arrays;  // by ascending place
+  std::vector<UploadCopy> copies;
+};
+
+// Arrays that follow each other within kStage bytes go up in one copy, from a host buffer of
+// their own: a copy costs about 10 us whatever its size, and a small graph has some twenty
+// arrays (2000 nodes: 0.75 -> 0.6 ms per erc_create).  Arrays above kStage / 2 go up by
+// themselves, and end the buffer before them: a buffer holds the gaps between its arrays too,
+// so that one which went on behind such an array would carry its place along.
+void gather_copies(Upload* U) {
+  constexpr int64_t kStage = 1 << 20;
+  bool open = false;  // the last copy is a buffer that may grow
+  for (const HostArray& a : U->arrays) {
+    if (a.bytes <= 0) continue;
+    if (a.bytes > kStage / 2) {
+      U->copies.push_back(UploadCopy{a.off, a.src, a.bytes, {}});
+      open = false;
+      continue;
+    }
+    if (open && a.off + a.bytes > U->copies.back().off + kStage) open = false;
+    if (!open) U->copies.push_back(UploadCopy{a.off, nullptr, 0, {}});
+    open = true;
+    UploadCopy& c = U->copies.back();
+    const char* x = static_cast<const char*>(a.src);
+    c.stage.resize(a.off - c.off);
+    c.stage.insert(c.stage.end(), x, x + a.bytes);
+    c.bytes = static_cast<int64_t>(c.stage.size());
+  }
+}
+
+void build_upload(const erc_graph_desc* d, const Canon& c, const Plan& P, const GraphLayout& L, Upload* U) {
+  const int64_t n = d->n, nnz = d->rowptr[n];
+  const void* w = d->w;
+  if (d->w != nullptr && d->w_dtype != d->solve_dtype) {
+    if (d->solve_dtype == ERC_F32) {
+      const double* x = static_cast<const double*>(d->w);
+      U->wf.resize(nnz);
+      for (int64_t k = 0; k < nnz; ++k) U->wf[k] = static_cast<float>(x[k]);
+      w = U->wf.data();
+    } else {
+      const float* x = static_cast<const float*>(d->w);
+      U->wd.resize(nnz);
+      for (int64_t k = 0; k < nnz; ++k) U->wd[k] = static_cast<double>(x[k]);
+      w = U->wd.data();
+    }
+  }
+  U->light.resize(P.light.size());
+  for (size_t k = 0; k < P.light.size(); ++k) {
+    const int32_t i = P.light[k];
+    U->light[k] = LightRow{d->rowptr[i], i, static_cast<int32_t>(d->rowptr[i + 1] - d->rowptr[i])};
+  }
+  auto add = [&](int64_t off, const void* src, int64_t bytes) { U->arrays.push_back(HostArray{off, src, bytes}); };
+  auto list = [&](int64_t off, const auto& v) { add(off, v.data(), static_cast<int64_t>(v.size() * sizeof(v[0]))); };
+  add(L.rowptr, d->rowptr, (n + 1) * 8);
+  add(L.col, d->col, nnz * 4);
+  if (w != nullptr) add(L.w, w, nnz * static_cast<int64_t>(dsize(d->solve_dtype)));
+  list(L.eid, c.eid);
+  list(L.sw, c.sw);
+  list(L.ubase, c.ubase);
+  list(L.deg, c.deg);
+  list(L.light, U->light);
+  list(L.wave_lo, P.wave_lo);
+  list(L.task_row, P.task_row);
+  list(L.task_mega, P.task_mega);
+  list(L.task_chunk, P.task_chunk);
+  list(L.task_beg, P.task_beg);
+  list(L.task_end, P.task_end);
+  list(L.mega_row, P.mega_row);
+  list(L.mega_nchunk, P.mega_nchunk);
+  list(L.mega_chunk0, P.mega_chunk0);
+  if (!P.res_row.empty()) {
+    list(L.res_row, P.res_row);
+    list(L.res_pos, P.res_pos);
+    list(L.res_off, P.res_off);
+    list(L.res_hpos, P.res_hpos);
+    list(L.res_hbeg, P.res_hbeg);
+    list(L.res_hlen, P.res_hlen);
+    list(L.res_hc0, P.res_hc0);
+  }
+  gather_copies(U);
+}
+
+// Whether the copies bring every byte of every array to its place, whatever their order: they
+// are apart from each other and each array's bytes stand in one of them.
+bool upload_complete(const Upload& U, int64_t total) {
+  int64_t end = 0;
+  for (const UploadCopy& c : U.copies) {
+    if (c.off < end || c.bytes <= 0) return false;
+    end = c.off + c.bytes;
+  }
+  if (end > total) return false;
+  size_t k = 0;
+  for (const HostArray& a : U.arrays) {
+    if (a.bytes <= 0) continue;
+    while (k < U.copies.size() && U.copies[k].off + U.copies[k].bytes <= a.off) ++k;
+    if (k == U.copies.size()) return false;
+    const UploadCopy& c = U.copies[k];
+    if (a.off < c.off || a.off + a.bytes > c.off + c.bytes) return false;
+    const char* at = static_cast<const char*>(c.data()) + (a.off - c.off);
+    if (at != a.src && std::memcmp(at, a.src, static_cast<size_t>(a.bytes)) != 0) return false;
+  }
+  return true;
+}
+
 // Workspace layout for a padded block width.
 struct WorkLayout {
   int64_t z, r, p, q, chunkbuf, mega_dots, rho, rr, rho0, thr, alpha, beta, active,
@@ -1084,31 +1207,8 @@ erc_status erc_create(const erc_graph_desc* desc, void* dev_mem, size_t bytes, v
         (!P.res_row.empty() && (P.res_off.back() + kResPadQuads > s.quads_max ||
                                 static_cast<int64_t>(P.res_hpos.size()) > s.hchunk_max)))
       return fail(ERC_E_STATE, "internal: work plan exceeds its size bound");
-    // weights in the working precision
-    std::vector<float> wf;
-    std::vector<double> wd;
-    const void* wsrc = nullptr;
-    if (weighted) {
-      if (desc->solve_dtype == ERC_F32) {
-        if (desc->w_dtype == ERC_F32) {
-          wsrc = desc->w;
-        } else {
-          wf.resize(nnz);
-          const double* x = static_cast<const double*>(desc->w);
-          for (int64_t k = 0; k < nnz; ++k) wf[k] = static_cast<float>(x[k]);
-          wsrc = wf.data();
-        }
-      } else {
-        if (desc->w_dtype == ERC_F64) {
-          wsrc = desc->w;
-        } else {
-          wd.resize(nnz);
-          const float* x = static_cast<const float*>(desc->w);
-          for (int64_t k = 0; k < nnz; ++k) wd[k] = static_cast<double>(x[k]);
-          wsrc = wd.data();
-        }
-      }
-    }
+    Upload U;
+    build_upload(desc, c, P, L, &U);
     auto* h = new erc_graph_s();
     h->n = n;
     h->nnz = nnz;
@@ -1144,64 +1244,11 @@ erc_status erc_create(const erc_graph_desc* desc, void* dev_mem, size_t bytes, v
     hipStream_t hs = static_cast<hipStream_t>(stream);
     hipError_t e = hipSuccess;
     auto chk = [&](hipError_t x) { if (e == hipSuccess) e = x; };
-    // arrays that follow each other within kStage bytes go up in one copy, from a host buffer
-    // that lives until the stream is drained: a copy costs about 10 us whatever its size, and
-    // a small graph has some twenty arrays (2000 nodes: 0.75 -> 0.6 ms per erc_create)
-    constexpr int64_t kStage = 1 << 20;
-    std::vector<std::vector<char>> stages;
-    int64_t stage_at = 0;  // offset of the open stage
-    std::vector<char> open;
-    auto flush = [&]() {
-      if (open.empty()) return;
-      chk(hipMemcpyAsync(base + stage_at, open.data(), open.size(), hipMemcpyHostToDevice, hs));
-      stages.push_back(std::move(open));
-      open.clear();
-    };
-    auto up = [&](int64_t off, const void* src, int64_t nbytes) -> hipError_t {
-      if (nbytes <= 0) return hipSuccess;
-      if (!open.empty() && (off < stage_at + static_cast<int64_t>(open.size()) ||
-                            off + nbytes > stage_at + kStage))
-        flush();
-      if (nbytes > kStage / 2) return hipMemcpyAsync(base + off, src, nbytes, hipMemcpyHostToDevice, hs);
-      if (open.empty()) stage_at = off;
-      open.resize(off - stage_at);
-      open.insert(open.end(), static_cast<const char*>(src), static_cast<const char*>(src) + nbytes);
-      return hipSuccess;
-    };
-    chk(up(L.rowptr, desc->rowptr, (n + 1) * 8));
-    chk(up(L.col, desc->col, nnz * 4));
-    if (weighted) chk(up(L.w, wsrc, nnz * static_cast<int64_t>(dsize(desc->solve_dtype))));
-    chk(up(L.eid, c.eid.data(), nnz * 4));
-    chk(up(L.sw, c.sw.data(), c.m * 8));
-    chk(up(L.ubase, c.ubase.data(), (n + 1) * 8));
-    chk(up(L.deg, c.deg.data(), n * 8));
-    std::vector<LightRow> lrows(P.light.size());
-    for (size_t k = 0; k < P.light.size(); ++k) {
-      const int32_t i = P.light[k];
-      lrows[k] = LightRow{desc->rowptr[i], i, static_cast<int32_t>(desc->rowptr[i + 1] - desc->rowptr[i])};
-    }
-    chk(up(L.light, lrows.data(), static_cast<int64_t>(lrows.size() * sizeof(LightRow))));
-    chk(up(L.wave_lo, P.wave_lo.data(), static_cast<int64_t>(P.wave_lo.size()) * 4));
+    for (const UploadCopy& u : U.copies)
+      chk(hipMemcpyAsync(base + u.off, u.data(), static_cast<size_t>(u.bytes), hipMemcpyHostToDevice, hs));
     const int64_t nt = static_cast<int64_t>(P.task_row.size());
-    chk(up(L.task_row, P.task_row.data(), nt * 4));
-    chk(up(L.task_mega, P.task_mega.data(), nt * 4));
-    chk(up(L.task_chunk, P.task_chunk.data(), nt * 4));
-    chk(up(L.task_beg, P.task_beg.data(), nt * 8));
-    chk(up(L.task_end, P.task_end.data(), nt * 8));
     const int64_t nm = static_cast<int64_t>(P.mega_nchunk.size());
-    chk(up(L.mega_row, P.mega_row.data(), nm * 4));
-    chk(up(L.mega_nchunk, P.mega_nchunk.data(), nm * 4));
-    chk(up(L.mega_chunk0, P.mega_chunk0.data(), nm * 4));
     const bool res = !P.res_row.empty();
-    if (res) {
-      chk(up(L.res_row, P.res_row.data(), static_cast<int64_t>(P.res_row.size()) * 4));
-      chk(up(L.res_pos, P.res_pos.data(), n * 2));
-      chk(up(L.res_off, P.res_off.data(), static_cast<int64_t>(P.res_off.size()) * 4));
-      chk(up(L.res_hpos, P.res_hpos.data(), static_cast<int64_t>(P.res_hpos.size()) * 4));
-      chk(up(L.res_hbeg, P.res_hbeg.data(), static_cast<int64_t>(P.res_hbeg.size()) * 4));
-      chk(up(L.res_hlen, P.res_hlen.data(), static_cast<int64_t>(P.res_hlen.size()) * 4));
-      chk(up(L.res_hc0, P.res_hc0.data(), static_cast<int64_t>(P.res_hc0.size()) * 4));
-    }
     DevGraph& g = h->dg;
     g.n = static_cast<int32_t>(n);
     g.nnz = nnz;
@@ -1252,7 +1299,6 @@ erc_status erc_create(const erc_graph_desc* desc, void* dev_mem, size_t bytes, v
       r.hlen = reinterpret_cast<const int32_t*>(base + L.res_hlen);
       r.hc0 = reinterpret_cast<const int32_t*>(base + L.res_hc0);
     }
-    flush();
     if (e == hipSuccess)
       chk(launch_endpoints(g, const_cast<int32_t*>(g.eu), const_cast<int32_t*>(g.ev), hs));
     if (res && e == hipSuccess) chk(launch_res_fill(g, h->dt, hs));
@@ -1833,6 +1879,10 @@ erc_status erc_debug_check_plan(const erc_graph_desc* desc) {
         if (upper && c.eid[pos] != c.ubase[u] + (pos - (rp[u + 1] - up))) return bad("edge id of an upper entry");
       }
     }
+    const GraphLayout L = graph_layout(s, desc->w != nullptr, desc->solve_dtype);
+    Upload U;
+    build_upload(desc, c, P, L, &U);
+    if (!upload_complete(U, L.total)) return bad("the copies do not bring every array to its place");
     return ERC_OK;
   });
 }
