@@ -254,6 +254,7 @@ struct SubgraphWork {
   uint32_t* nprefix;    // rank of each node word's first bit
   uint32_t* cnt;        // up to n: edges per kept node, then their prefix sums (node draws)
   uint32_t* tile;       // tile sums
+  uint8_t* flags;       // a byte per item (32 per bitmap word), for marks of many items
 };
 hipError_t launch_draw(const double* prob, int64_t N, int64_t draws, uint64_t base,
                        const DrawWork& w, int64_t* idx, hipStream_t s);

@@ -8,10 +8,13 @@
 //        items, exclusive prefix sums of the tiles and, within each, of its subtiles of 16,
 //        and per draw the target t = floor(X T / 2^128) from two SplitMix64 words and the
 //        item i with C_i <= t < C_{i+1}, found tile, subtile, item
-//   k_mark, k_bits_up, k_bits_down       the drawn items as a bitmap, its population counts,
-//        and from it the kept ids in increasing order and the rank of every kept node
+//   k_mark (k_flag and k_pack for many draws), k_bits_up, k_bits_down   the drawn items as a
+//        bitmap, its population counts, and from it the kept ids in increasing order and the
+//        rank of every kept node
 //   k_count_edges, k_count_up, k_count_down, k_emit_edges   the subgraph induced on the kept
 //        nodes, from their rows alone
+//   k_edge_bits, k_kept_ends             the same from the list of all edges, where a good part
+//        of the nodes is kept
 //   k_endpoints_of, k_renumber           the endpoints of the kept edges
 //
 // What bounds it: a draw reads every probability once (31M edges: 250 MB) and writes 1/16 of
@@ -278,6 +281,36 @@ __global__ __launch_bounds__(kBlock) void k_mark(const int64_t* __restrict__ idx
   }
 }
 
+// Marks of many items: a plain store into a byte per item, which k_pack makes bits of.  Atomics
+// run at about 15 per ns (4.8M draws of 1.2M nodes: 312 us to mark bits, where stores take
+// about 55), but bytes have to be cleared and read.
+__global__ __launch_bounds__(kBlock) void k_flag(const int64_t* __restrict__ idx,
+                                                 int64_t count, int64_t N,
+                                                 uint8_t* __restrict__ flags,
+                                                 uint32_t* status) {
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
+  for (int64_t d = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; d < count;
+       d += stride) {
+    const int64_t i = idx[d];
+    if (i < 0 || i >= N) atomicOr(status, kSubBadIndex);
+    else flags[i] = 1;
+  }
+}
+
+// One thread per bitmap word: 32 bytes of 0 or 1 to its bits, four bytes to four bits by one
+// product (the ten partial products fall on different bits).
+__global__ __launch_bounds__(kBlock) void k_pack(const uint8_t* __restrict__ flags,
+                                                 uint32_t* __restrict__ bits) {
+  const int64_t w = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
+  const uint4* f = reinterpret_cast<const uint4*>(flags) + w * 2;
+  const uint4 a = f[0], b = f[1];
+  const uint32_t x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+  uint32_t out = 0;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) out |= ((x[k] * 0x01020408u) >> 24) << (4 * k);
+  bits[w] = out;
+}
+
 // One block per bitmap tile, four words (a 16-byte load) per thread; the bitmaps are 16-byte
 // aligned and padded to whole tiles by the host layout.  Tiles of 1024 words spread the few
 // set bits of a draw over enough blocks (nodes of the 1.2M-node case: 6.4 us against 16.0 with
@@ -451,12 +484,54 @@ __global__ __launch_bounds__(kBlock) void k_emit_edges(DevGraph g, const uint32_
   }
 }
 
-// Endpoints of the kept edges (old numbering) and their bits.
+// Bits of the edges whose ends are both kept, for draws that keep a good part of the nodes: every
+// edge once, in order, where the rows' upper parts are short and uneven.  A wavefront takes
+// 256 edges, four per lane; every word of the bitmap is written.  What bounds it: the list
+// (8 bytes per edge) and the lookups, which hit the caches.
+__global__ __launch_bounds__(kBlock) void k_edge_bits(DevGraph g, const uint32_t* __restrict__ bits,
+                                                      uint64_t* __restrict__ ebits) {
+  const int lane = threadIdx.x & 63;
+  const int64_t e0 = (static_cast<int64_t>(blockIdx.x) * kWavesPerBlock + (threadIdx.x >> 6)) * 256;
+  int32_t u[4], v[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int64_t e = e0 + k * 64 + lane;
+    u[k] = g.eu[e < g.m ? e : g.m - 1];
+    v[k] = g.ev[e < g.m ? e : g.m - 1];
+  }
+  uint64_t mine = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const uint64_t m = __ballot(is_set(bits, u[k]) & is_set(bits, v[k]) & (e0 + k * 64 + lane < g.m));
+    if (lane == k) mine = m;
+  }
+  if (lane < 4) ebits[e0 / 64 + lane] = mine;
+}
+
+// New numbers of the kept edges' ends.
+__global__ __launch_bounds__(kBlock) void k_kept_ends(DevGraph g, const int64_t* __restrict__ edges,
+                                                      const uint32_t* __restrict__ mkept,
+                                                      const uint32_t* __restrict__ bits,
+                                                      const uint32_t* __restrict__ prefix,
+                                                      int32_t* __restrict__ uo,
+                                                      int32_t* __restrict__ vo) {
+  const int64_t m = *mkept;
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
+  for (int64_t k = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; k < m; k += stride) {
+    const int64_t e = edges[k];
+    uo[k] = static_cast<int32_t>(rank_of(bits, prefix, g.eu[e]));
+    vo[k] = static_cast<int32_t>(rank_of(bits, prefix, g.ev[e]));
+  }
+}
+
+// Endpoints of the kept edges (old numbering) and their marks, bits or (FLAGS) bytes.
+template <bool FLAGS>
 __global__ __launch_bounds__(kBlock) void k_endpoints_of(DevGraph g, const int64_t* __restrict__ edges,
                                                          const uint32_t* __restrict__ mkept,
                                                          int32_t* __restrict__ uo,
                                                          int32_t* __restrict__ vo,
-                                                         uint32_t* __restrict__ bits) {
+                                                         uint32_t* __restrict__ bits,
+                                                         uint8_t* __restrict__ flags) {
   const int64_t m = *mkept;
   const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
   for (int64_t k = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; k < m; k += stride) {
@@ -466,8 +541,14 @@ __global__ __launch_bounds__(kBlock) void k_endpoints_of(DevGraph g, const int64
     vo[k] = v;
     // edges run by u: one of a run of equal u marks it
     const int prev = __shfl_up(lo, 1);
-    if ((threadIdx.x & 63) == 0 || prev != lo) set_bit(bits, lo);
-    set_bit(bits, v);
+    const bool first = (threadIdx.x & 63) == 0 || prev != lo;
+    if constexpr (FLAGS) {
+      if (first) flags[lo] = 1;
+      flags[v] = 1;
+    } else {
+      if (first) set_bit(bits, lo);
+      set_bit(bits, v);
+    }
   }
 }
 
@@ -507,6 +588,33 @@ hipError_t launch_draw(const double* prob, int64_t N, int64_t draws, uint64_t ba
   return hipGetLastError();
 }
 
+// Whether `count` marks of N items go through bytes: where their atomics (15 per ns) take
+// longer than clearing and packing the bytes (2 N at 4 TB/s) and two launches.  Whole subgraph
+// calls, bits against bytes: 310,200 draws of 31M edges 0.18 against 0.10 ms, 3.1M 0.67 against
+// 0.25; 480,000 of 4.8M 0.17 against 0.09; 33,000 of 110,000 (bits either way) 0.08.
+constexpr int64_t kFlagMin = 65536;
+static bool by_flags(int64_t count, int64_t N) { return count > kFlagMin && count > N / 64; }
+
+// The marks that `mark` leaves (bits into `bits`, or bytes into w.flags) as a bitmap of N items.
+template <typename Mark>
+static hipError_t marked(bool flags, int64_t N, const SubgraphWork& w, uint32_t* bits, hipStream_t s, Mark mark) {
+  if (flags) {
+    const hipError_t e = launch_fill_u32(reinterpret_cast<uint32_t*>(w.flags), 0u, sub_words(N) * 8, s);
+    if (e != hipSuccess) return e;
+  }
+  mark();
+  if (flags) ERC_DLAUNCH(k_pack, sub_words(N) / kBlock, s, w.flags, bits);
+  return hipGetLastError();
+}
+
+// Node draws of at least this share of the nodes look at every edge, fewer at the rows of the
+// kept nodes.  Whole calls, rows against every edge: 1.2M nodes and 31M edges, draws of 1/100 of
+// the nodes 0.12 against 0.16 ms, 1/10 0.23 against 0.21, as many as nodes 0.71 against 0.45,
+// four times as many 1.18 against 0.67 (with marks by bits, and rows, 1.47; flags per edge and
+// two walks over all rows had taken 1.32); 1.2M nodes and 4.8M edges, 1/100 0.08 either way,
+// 1/10 0.15 against 0.09, four times as many 0.70 against 0.17 (0.98; 0.42).
+constexpr int64_t kEveryEdge = 16;
+
 hipError_t launch_subgraph(const DevGraph& g, int items, const int64_t* idx, int64_t count,
                            const SubgraphWork& w, int32_t* nodes, int64_t* edges, int32_t* uo,
                            int32_t* vo, hipStream_t s) {
@@ -517,13 +625,25 @@ hipError_t launch_subgraph(const DevGraph& g, int items, const int64_t* idx, int
   // the head and the bitmaps follow each other: one fill
   hipError_t err = launch_fill_u32(w.head, 0u, w.clear_words, s);
   if (err != hipSuccess) return err;
+  auto mark = [&](int64_t N, uint32_t* bits) {
+    const bool flags = by_flags(count, N);
+    return marked(flags, N, w, bits, s, [&]() {
+      if (flags) ERC_DLAUNCH(k_flag, blocks_for(count, kBlock), s, idx, count, N, w.flags, status);
+      else if (count > 0) ERC_DLAUNCH(k_mark, blocks_for(count, kBlock), s, idx, count, N, bits, status);
+    });
+  };
   if (items == 0) {
-    if (count > 0) ERC_DLAUNCH(k_mark, blocks_for(count, kBlock), s, idx, count,
-                               static_cast<int64_t>(g.n), w.nbits, status);
+    if ((err = mark(g.n, w.nbits)) != hipSuccess) return err;
     ERC_DLAUNCH(k_bits_up, ntile, s, w.nbits, w.tile);
     ERC_DLAUNCH(k_bits_down<int32_t>, ntile, s, w.nbits, w.tile, w.nprefix, nodes, nkept);
     const int64_t most = count < g.n ? count : g.n;
-    if (most > 0 && g.m > 0) {
+    if (most > 0 && g.m > 0 && count >= g.n / kEveryEdge) {
+      ERC_DLAUNCH(k_edge_bits, sub_words(g.m) * 32 / (256 * kWavesPerBlock), s, g, w.nbits,
+                  reinterpret_cast<uint64_t*>(w.ebits));
+      ERC_DLAUNCH(k_bits_up, mtile, s, w.ebits, w.tile);
+      ERC_DLAUNCH(k_bits_down<int64_t>, mtile, s, w.ebits, w.tile, static_cast<uint32_t*>(nullptr), edges, mkept);
+      ERC_DLAUNCH(k_kept_ends, blocks_for(g.m, kBlock), s, g, edges, mkept, w.nbits, w.nprefix, uo, vo);
+    } else if (most > 0 && g.m > 0) {
       const int grid = blocks_for(most, kWavesPerBlock);
       ERC_DLAUNCH(k_count_edges, grid, s, g, w.nbits, nodes, nkept, w.cnt);
       ERC_DLAUNCH(k_count_up, scan_blocks(most), s, w.cnt, nkept, w.tile);
@@ -533,11 +653,16 @@ hipError_t launch_subgraph(const DevGraph& g, int items, const int64_t* idx, int
   } else if (count > 0) {  // (the host refuses drawn edges of a graph without any)
     const int64_t most = count < g.m ? count : g.m;
     const int grid = blocks_for(most, kBlock);
-    ERC_DLAUNCH(k_mark, blocks_for(count, kBlock), s, idx, count, g.m, w.ebits, status);
+    if ((err = mark(g.m, w.ebits)) != hipSuccess) return err;
     ERC_DLAUNCH(k_bits_up, mtile, s, w.ebits, w.tile);
     ERC_DLAUNCH(k_bits_down<int64_t>, mtile, s, w.ebits, w.tile, static_cast<uint32_t*>(nullptr), edges,
                 mkept);
-    ERC_DLAUNCH(k_endpoints_of, grid, s, g, edges, mkept, uo, vo, w.nbits);
+    const bool flags = by_flags(most, g.n);
+    err = marked(flags, g.n, w, w.nbits, s, [&]() {
+      if (flags) ERC_DLAUNCH(k_endpoints_of<true>, grid, s, g, edges, mkept, uo, vo, w.nbits, w.flags);
+      else ERC_DLAUNCH(k_endpoints_of<false>, grid, s, g, edges, mkept, uo, vo, w.nbits, w.flags);
+    });
+    if (err != hipSuccess) return err;
     ERC_DLAUNCH(k_bits_up, ntile, s, w.nbits, w.tile);
     ERC_DLAUNCH(k_bits_down<int32_t>, ntile, s, w.nbits, w.tile, w.nprefix, nodes, nkept);
     ERC_DLAUNCH(k_renumber, grid, s, w.nbits, w.nprefix, mkept, uo, vo);

@@ -1616,7 +1616,7 @@ DrawLayout draw_layout(int64_t N) {
 }
 constexpr int64_t kSubAlign = 16;
 struct SubLayout {
-  int64_t head, nbits, ebits, nprefix, cnt, tile, total;
+  int64_t head, nbits, ebits, nprefix, cnt, tile, flags, total;
 };
 SubLayout sub_layout(const erc_graph_s* h) {
   SubLayout L{};
@@ -1632,8 +1632,8 @@ SubLayout sub_layout(const erc_graph_s* h) {
   L.nprefix = take(sub_words(h->n) * 4);
   L.cnt = take(h->n * 4);
   L.tile = take(std::max({sub_words(h->n) / kBitTile, sub_words(h->m) / kBitTile, scan_blocks(h->n)}) * 4);
-  L.total = off + kSubAlign;  // the bitmaps are read 16 bytes at a time
-
+  L.flags = take(std::max(sub_words(h->n), sub_words(h->m)) * 32);
+  L.total = off + kSubAlign;  // the bitmaps and flags are read 16 bytes at a time
   return L;
 }
 // `words` device words to the handle's pinned slot, waited for: a copy to pageable memory
@@ -1731,6 +1731,7 @@ erc_status erc_subgraph(erc_handle h, erc_items items, const int64_t* idx_dev, i
     w.nprefix = reinterpret_cast<uint32_t*>(b + L.nprefix);
     w.cnt = reinterpret_cast<uint32_t*>(b + L.cnt);
     w.tile = reinterpret_cast<uint32_t*>(b + L.tile);
+    w.flags = reinterpret_cast<uint8_t*>(b + L.flags);
     hipStream_t s = static_cast<hipStream_t>(stream);
     ERC_HIP(launch_subgraph(h->dg, items == ERC_NODES ? 0 : 1, idx_dev, count, w, nodes_dev,
                             edges_dev, u_dev, v_dev, s));

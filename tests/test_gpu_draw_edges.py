@@ -76,3 +76,44 @@ def test_subgraph_scratch_at_an_odd_address():
     got = G.subgraph("nodes", torch.from_numpy(idx).cuda())
     want = OS.node_subgraph(g, idx)
     np.testing.assert_array_equal(got["edges"].cpu().numpy(), want["edges"])
+
+
+def _random_graph(n, m, seed):
+    rng = np.random.default_rng(seed)
+    u, v = rng.integers(0, n, m), rng.integers(0, n, m)
+    return gen.from_edges(n, u[u != v], v[u != v])
+
+
+@pytest.mark.parametrize("n,m,count", [
+    # marks by bits up to 65,536 draws, by bytes above; every edge from n / 16 node draws on
+    (1000, 5000, 65536), (1000, 5000, 65537), (1000, 32768, 70000), (40000, 33000, 65537),
+    (20000, 65536, 1249), (20000, 65536, 1250), (20000, 65700, 1251), (33, 400, 1), (33, 400, 2), (2, 1, 1),
+    # more than 64 items per draw keep the bits
+    (5000000, 4300000, 66000), (5000000, 4300000, 79000)])
+@pytest.mark.parametrize("items", ["nodes", "edges"])
+def test_subgraph_of_many_draws(n, m, count, items):
+    E = _gpu()
+    g = _random_graph(n, m, n + m) if n > 2 else gen.path_graph(2)
+    G = E.Graph(g.rowptr, g.col, g.w)
+    rng = np.random.default_rng(count)
+    N = n if items == "nodes" else g.m
+    # half of the draws fall on a tenth of the items
+    idx = np.where(rng.random(count) < 0.5, rng.integers(0, N, count), rng.integers(0, N // 10 + 1, count))
+    idx[-1] = N - 1
+    got = G.subgraph(items, torch.from_numpy(idx).cuda())
+    want = (OS.node_subgraph if items == "nodes" else OS.edge_subgraph)(g, idx)
+    for k in ("nodes", "edges", "u", "v"):
+        np.testing.assert_array_equal(got[k].cpu().numpy(), want[k])
+
+
+@pytest.mark.parametrize("bad", [-1, 1000])
+def test_bad_index_among_many_draws(bad):
+    E = _gpu()
+    from paper_2609_27209_amd import _abi
+    g = _random_graph(1000, 5000, 3)
+    G = E.Graph(g.rowptr, g.col, g.w)
+    idx = torch.arange(70000, dtype=torch.int64, device="cuda") % 1000
+    idx[12345] = bad
+    with pytest.raises(_abi.ErcError) as ei:
+        G.subgraph("nodes", idx)
+    assert ei.value.status == _abi.ERC_E_INVALID_ARG
