@@ -70,7 +70,9 @@ typedef struct erc_graph_s* erc_handle;
  *              ERC_F32 the dot products, R, p, kappa and the probabilities are
  *              still fp64, and the SpMM sums the rows it runs as block tasks
  *              (more than max(1024, two wavefront shares) entries) in fp64 and the
- *              other rows in fp32
+ *              other rows in fp32; graphs solved by a single launch (see
+ *              erc_resistance) add rows of up to 128 entries by fours in fp32 and the
+ *              fours in fp64, longer rows in fp64
  * The structure must be symmetric with no self-loops and no repeated entries; each
  * undirected edge is stored twice.  Isolated nodes are allowed. */
 typedef struct {

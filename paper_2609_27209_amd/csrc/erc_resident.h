@@ -8,7 +8,7 @@
 // launch, grid-wide reduction or host poll sits between iterations.
 //
 // What bounds it: on the smallest graphs the chain of reductions, barriers and LDS round
-// trips of an iteration (2000 rows: 3.1 us in fp32, 5.2 us in fp64), on larger ones the LDS
+// trips of an iteration (2000 rows: 3.7 us in fp32, 4.9 us in fp64), on larger ones the LDS
 // gathers, whose random banks collide (64-lane gathers take 7 cycles instead of 2), and the
 // vector instructions around them (20,000 rows, 220,000 entries: 20.6 us; LDS busy 61% of
 // the time, over half of it conflicts, vector units 49%), with the operator's stream from the
@@ -17,12 +17,17 @@
 // launches each.  Whole steps: 2000 rows fp64 1.19 -> 0.35 ms, 2000 rows and 1024 columns
 // 16.5 -> 0.70 ms, 20,000 rows 1.95 -> 0.92 ms, 12,305 rows fp64 Jacobi 4.8 -> 1.3 ms.
 //
-// The recurrence is Hestenes-Stiefel CG with the stopping rule and the precision of the
-// block kernels: fp32 or fp64 vectors, inner products in fp64 or double-double, rows above
-// kResHeavy entries summed in fp64.  In fp64 beta also has their expanded form, so that rows
-// which both sum one entry after the other give the same bits from both (fp64 CG is where a
-// caller looks for agreement beyond the stopping tolerance, and a few ten iterations amplify
-// the last bit of a beta to 1e-8 of the solution); fp32 takes r.r of the stored r.
+// The recurrence is Hestenes-Stiefel CG with the stopping rule of the block kernels, and no sum
+// is less precise than theirs: fp32 or fp64 vectors; a thread's part of an inner product in fp64
+// or double-double, the threads' parts folded as compensated pairs; in fp32 a row's entries in
+// fours, and the fours (of rows above kResHeavy entries each entry) added in fp64.  (fp32 chains
+// over the row put weighted rows of about 100 entries 1.7 times as far from the fp64 solution
+// as the block kernels, and plain folds saved 0.5 us an iteration.)  In fp64 beta also has
+// their expanded form, so that rows which both sum one entry after the other give the same bits
+// from both (fp64 CG is where a caller looks for agreement beyond the stopping tolerance, and a
+// few ten iterations amplify the last bit of a beta to 1e-8 of the solution); fp32 takes r.r of
+// the stored r, which needs slightly fewer iterations on power-law graphs than the expansion and
+// lies no further from the fp64 solution.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -80,31 +85,42 @@ __device__ __forceinline__ void two_sum(double a, double b, double& s, double& e
   e = (a - (s - z)) + (b - z);
 }
 
-// Inner products in twice the working precision: fp64 sums of exact fp32 products, or
-// double-double sums of exactly split fp64 products.
+__device__ __forceinline__ DD dd_add(DD a, DD b) {
+#pragma clang fp contract(off)
+  double s, e;
+  two_sum(a.s, b.s, s, e);
+  return DD{s, (a.c + b.c) + e};
+}
+__device__ __forceinline__ double dd_value(DD a) { return a.s + a.c; }
+__device__ __forceinline__ DD dd_times(DD a, double b) {
+#pragma clang fp contract(off)
+  const double p = a.s * b;
+  const double pe = fma(a.s, b, -p);
+  const double c = pe + a.c * b;
+  DD r;
+  two_sum(p, c, r.s, r.c);
+  return r;
+}
+
+// Inner products in twice the working precision, as in the block kernels: a thread adds
+// exact fp32 products in fp64, or exactly split fp64 products in double-double, and the threads'
+// sums are folded as compensated pairs.
 template <typename T>
 struct Acc;
 template <>
 struct Acc<float> {
-  typedef double V;
-  __device__ __forceinline__ static V zero() { return 0.0; }
-  __device__ __forceinline__ static V add(V a, V b) { return a + b; }
-  __device__ __forceinline__ static V mac(V a, float x, float y) {
+  typedef double L;
+  __device__ __forceinline__ static L zero() { return 0.0; }
+  __device__ __forceinline__ static L mac(L a, float x, float y) {
     return fma(static_cast<double>(x), static_cast<double>(y), a);
   }
-  __device__ __forceinline__ static double value(V a) { return a; }
+  __device__ __forceinline__ static DD pair(L a) { return DD{a, 0.0}; }
 };
 template <>
 struct Acc<double> {
-  typedef DD V;
-  __device__ __forceinline__ static V zero() { return DD{0.0, 0.0}; }
-  __device__ __forceinline__ static V add(V a, V b) {
-#pragma clang fp contract(off)
-    double s, e;
-    two_sum(a.s, b.s, s, e);
-    return DD{s, (a.c + b.c) + e};
-  }
-  __device__ __forceinline__ static V mac(V a, double x, double y) {
+  typedef DD L;
+  __device__ __forceinline__ static L zero() { return DD{0.0, 0.0}; }
+  __device__ __forceinline__ static L mac(L a, double x, double y) {
 #pragma clang fp contract(off)
     const double p = x * y;
     const double pe = fma(x, y, -p);
@@ -112,16 +128,7 @@ struct Acc<double> {
     two_sum(a.s, p, t, e);
     return DD{t, a.c + (e + pe)};
   }
-  __device__ __forceinline__ static double value(V a) { return a.s + a.c; }
-  __device__ __forceinline__ static V times(V a, double b) {
-#pragma clang fp contract(off)
-    const double p = a.s * b;
-    const double pe = fma(a.s, b, -p);
-    const double c = pe + a.c * b;
-    V r;
-    two_sum(p, c, r.s, r.c);
-    return r;
-  }
+  __device__ __forceinline__ static DD pair(L a) { return a; }
 };
 
 // Lane exchanges within 16-lane rows by DPP (a few cycles each, against an LDS round trip
@@ -137,29 +144,54 @@ template <int CTRL>
 __device__ __forceinline__ DD dpp(DD x) {
   return DD{dpp<CTRL>(x.s), dpp<CTRL>(x.c)};
 }
-__device__ __forceinline__ double at_lane(double x, int l) {
-  const long long b = __double_as_longlong(x);
-  const int lo = __builtin_amdgcn_readlane(static_cast<int>(b), l);
-  const int hi = __builtin_amdgcn_readlane(static_cast<int>(b >> 32), l);
-  return __longlong_as_double((static_cast<long long>(hi) << 32) | static_cast<unsigned>(lo));
-}
-__device__ __forceinline__ DD at_lane(DD x, int l) { return DD{at_lane(x.s, l), at_lane(x.c, l)}; }
+__device__ __forceinline__ double plus(double a, double b) { return a + b; }
+__device__ __forceinline__ DD plus(DD a, DD b) { return dd_add(a, b); }
 
-// Sum over each 16-lane row, in every lane of the row (the same bits in each).
-template <typename A>
-__device__ __forceinline__ typename A::V row_sum(typename A::V x) {
-  x = A::add(x, dpp<0xB1>(x));   // lanes xor 1
-  x = A::add(x, dpp<0x4E>(x));   // lanes xor 2
-  x = A::add(x, dpp<0x141>(x));  // the other four of eight
-  x = A::add(x, dpp<0x140>(x));  // the other eight of sixteen
+// Sum over each row of 16 (or 8) lanes, in every lane of the row (the same bits in each).
+template <int LANES, typename V>
+__device__ __forceinline__ V row_sum(V x) {
+  x = plus(x, dpp<0xB1>(x));   // lanes xor 1
+  x = plus(x, dpp<0x4E>(x));   // lanes xor 2
+  x = plus(x, dpp<0x141>(x));  // the other four of eight
+  if constexpr (LANES == 16) x = plus(x, dpp<0x140>(x));  // the other eight of sixteen
   return x;
 }
-template <typename A>
-__device__ __forceinline__ typename A::V wave_sum(typename A::V x) {
-  x = row_sum<A>(x);
-  return A::add(A::add(at_lane(x, 0), at_lane(x, 16)), A::add(at_lane(x, 32), at_lane(x, 48)));
+// a, b: x of a lane's row of 16 and of the row beside it (K = 16), or of its half of the
+// wavefront and of the other (K = 32), in one order for both; a lane swap gives both words at
+// once.  across: their sum.
+template <int K>
+__device__ __forceinline__ void swapped(double x, double& a, double& b) {
+  const long long v = __double_as_longlong(x);
+  const unsigned lo = static_cast<unsigned>(v), hi = static_cast<unsigned>(v >> 32);
+  if constexpr (K == 16) {
+    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    a = __longlong_as_double((static_cast<long long>(h[0]) << 32) | l[0]);
+    b = __longlong_as_double((static_cast<long long>(h[1]) << 32) | l[1]);
+  } else {
+    const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    a = __longlong_as_double((static_cast<long long>(h[0]) << 32) | l[0]);
+    b = __longlong_as_double((static_cast<long long>(h[1]) << 32) | l[1]);
+  }
 }
-
+template <int K>
+__device__ __forceinline__ double across(double x) {
+  double a, b;
+  swapped<K>(x, a, b);
+  return a + b;
+}
+template <int K>
+__device__ __forceinline__ DD across(DD x) {
+  DD a, b;
+  swapped<K>(x.s, a.s, b.s);
+  swapped<K>(x.c, a.c, b.c);
+  return dd_add(a, b);
+}
+template <typename V>
+__device__ __forceinline__ V wave_sum(V x) {
+  return across<32>(across<16>(row_sum<16>(x)));
+}
 // Makes a uniform address opaque, so that loads through it are not kept in registers across
 // the point (hoisted out of the iteration, or shared between its start and its end): the
 // registers hold z, r and q, and the reloads hit the caches.  The result names its address
@@ -258,13 +290,12 @@ struct Count {
 template <typename T, int NT, int RPT, bool W, bool PC, bool QL, int NQ>
 __global__ __launch_bounds__(NT) void k_resident(ResArgs a) {
   typedef Acc<T> A;
-  typedef typename A::V AV;
   constexpr int NW = NT / 64;
   constexpr int D = W && sizeof(T) == 8 ? 2 : 4;  // quads in flight per wavefront
   static_assert(D <= kResPadQuads, "the stream is read D quads past its end");
   __shared__ T s_p[RPT * NT];
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  AV (*s_red)[NW] = reinterpret_cast<AV (*)[NW]>(smem);
+  DD (*s_red)[NW] = reinterpret_cast<DD (*)[NW]>(smem);
   double* s_h = reinterpret_cast<double*>(&s_red[kResSums][0]);
   T* s_q = reinterpret_cast<T*>(s_h + ((a.p.nchunk + 1) & ~1));
 
@@ -273,25 +304,24 @@ __global__ __launch_bounds__(NT) void k_resident(ResArgs a) {
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = blockIdx.x;
   const T* __restrict__ Y = static_cast<const T*>(a.y) + c;
-  const T dlt = static_cast<T>(a.delta);
   // the wavefront's quads: lane s holds the end of slot s
   const int t0 = a.p.off[wv * RPT];
   const int ends = a.p.off[wv * RPT + min(lane + 1, RPT)];
 
   // sums over the workgroup of K values at once, in every thread; partial set b is free
   // again when the barrier after the next has passed (set 0: up to four sums, set 1: one)
-  auto block_sums = [&](AV* x, auto kk, int b) {
+  auto block_sums = [&](const typename A::L* x, DD* sum, auto kk, int b) {
     constexpr int K = decltype(kk)::value;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      const AV t = wave_sum<A>(x[k]);
+      const DD t = wave_sum(A::pair(x[k]));
       if (lane == 0) s_red[4 * b + k][wv] = t;
     }
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < K; ++k) x[k] = row_sum<A>((lane & 15) < NW ? s_red[4 * b + k][lane & (NW - 1)] : A::zero());
+    for (int k = 0; k < K; ++k) sum[k] = row_sum<NW>(s_red[4 * b + k][lane & (NW - 1)]);
   };
-  static_assert(NW <= 16, "row_sum adds 16 partials");
+  static_assert(NW == 8 || NW == 16, "row_sum adds 8 or 16 partials");
 
   Quad<T, W> own[NQ > 0 ? NQ : 1];
   if constexpr (NQ > 0) {
@@ -308,7 +338,8 @@ __global__ __launch_bounds__(NT) void k_resident(ResArgs a) {
   constexpr bool X = sizeof(T) == 8;
   constexpr int R = PC ? 2 : 1;
   constexpr int ND = X ? R + 2 : R;
-  AV dot[4] = {A::zero(), A::zero(), A::zero(), A::zero()};
+  typename A::L dot[4] = {A::zero(), A::zero(), A::zero(), A::zero()};
+  DD sum[4];
 #pragma unroll
   for (int s = 0; s < RPT; ++s) {
     const int pos = s * NT + tid;
@@ -323,11 +354,10 @@ __global__ __launch_bounds__(NT) void k_resident(ResArgs a) {
     s_p[pos] = p0;
     if (s % 4 == 3) asm volatile("" ::: "memory");  // no more than four slots' addresses at once
   }
-  if constexpr (PC) block_sums(dot, Count<2>(), 0);
-  else block_sums(dot, Count<1>(), 0);  // its barrier also completes p
-  const double rho0 = A::value(dot[0]);
+  block_sums(dot, sum, Count<R>(), 0);  // its barrier also completes p
+  const double rho0 = dd_value(sum[0]);
   double rr = rho0;
-  double rho = PC ? A::value(dot[1]) : rho0;
+  double rho = PC ? dd_value(sum[1]) : rho0;
   const double thr = a.tol2 * rho0;
   int iters = 0, status = 0;
   bool active = rr > 0.0;
@@ -354,13 +384,13 @@ __global__ __launch_bounds__(NT) void k_resident(ResArgs a) {
 #pragma unroll
       for (int u = 0; u < K; ++u)
         acc += static_cast<double>(w[u]) * (pi - static_cast<double>(s_p[j[u]]));
-      acc = wave_sum<Acc<float>>(acc);
+      acc = wave_sum(acc);
       if (lane == 0) s_h[h] = acc;
     }
     if (a.p.nchunk > 0) __syncthreads();
     // 2. q = (L + delta I) p, one row per lane: the wavefront's quads are one stream through
     // its slots, D of them in flight; at a slot's end its rows are finished
-    AV pq[1] = {A::zero()};
+    typename A::L pq[1] = {A::zero()};
     {
       const Global<const uint16_t> idx = fresh(a.p.idx);
       const Global<const T> wq = fresh(static_cast<const T*>(a.p.w));
@@ -373,22 +403,22 @@ __global__ __launch_bounds__(NT) void k_resident(ResArgs a) {
       }
       int t = t0, slot = 0;
       int te = __builtin_amdgcn_readlane(ends, 0);
-      T acc = T(0);
+      // an fp32 row adds the sums of its quads in fp64, an fp64 row its entries one by one
+      double acc = 0.0;
       T pi = s_p[tid], pn = s_p[min(1, RPT - 1) * NT + tid];  // this slot's p and the next's
       auto finish = [&]() {
         const int pos = slot * NT + tid;
-        T q = dlt * pi + acc;
         if (slot * NT < a.p.nheavy && pos < a.p.nheavy) {
-          double sum = 0.0;
-          for (int h = a.p.hc0[pos]; h < a.p.hc0[pos + 1]; ++h) sum += s_h[h];
-          q = static_cast<T>(a.delta * static_cast<double>(pi) + sum);
+          acc = 0.0;
+          for (int h = a.p.hc0[pos]; h < a.p.hc0[pos + 1]; ++h) acc += s_h[h];
         }
+        const T q = static_cast<T>(a.delta * static_cast<double>(pi) + acc);
         if (pos < a.n) {
           if (QL) s_q[pos] = q;
           else gq[pos] = q;
         }
         pq[0] = A::mac(pq[0], pi, q);
-        acc = T(0);
+        acc = 0.0;
         ++slot;
         te = __builtin_amdgcn_readlane(ends, slot);
         pi = pn;
@@ -398,10 +428,19 @@ __global__ __launch_bounds__(NT) void k_resident(ResArgs a) {
         T x[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) x[u] = at_position<T>(s_p, e.j[u / 2], u & 1);
+        if constexpr (X) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          if constexpr (W) acc += e.w[u] * (pi - x[u]);
-          else acc += pi - x[u];
+          for (int u = 0; u < 4; ++u) {
+            if constexpr (W) acc += e.w[u] * (pi - x[u]);
+            else acc += pi - x[u];
+          }
+        } else if constexpr (W) {
+          T t = e.w[0] * (pi - x[0]);
+#pragma unroll
+          for (int u = 1; u < 4; ++u) t += e.w[u] * (pi - x[u]);
+          acc += static_cast<double>(t);
+        } else {
+          acc += static_cast<double>(((pi - x[0]) + (pi - x[1])) + ((pi - x[2]) + (pi - x[3])));
         }
       };
       // (one way into the loop and gotos out of it: every path to a step then has the same
@@ -436,8 +475,8 @@ __global__ __launch_bounds__(NT) void k_resident(ResArgs a) {
       }
     done:;
     }
-    block_sums(pq, Count<1>(), 1);
-    const double pqv = A::value(pq[0]);
+    block_sums(pq, sum, Count<1>(), 1);
+    const double pqv = dd_value(sum[0]);
     active = pqv > 0.0 && isfinite(pqv);
     status = active ? 0 : 1;
     if (active) {
@@ -463,9 +502,9 @@ __global__ __launch_bounds__(NT) void k_resident(ResArgs a) {
         if constexpr (PC) dot[1] = here(A::mac(dot[1], r[s], mv[pos] * r[s]));
         if (s % (X ? 2 : 8) == (X ? 1 : 7)) asm volatile("" ::: "memory");
       }
-      block_sums(dot, Count<ND>(), 0);
-      rr = A::value(dot[0]);
-      const double rs = PC ? A::value(dot[1]) : rr;
+      block_sums(dot, sum, Count<ND>(), 0);
+      rr = dd_value(sum[0]);
+      const double rs = PC ? dd_value(sum[1]) : rr;
       ++iters;
       if (!(rr > thr)) {
         active = false;
@@ -479,8 +518,8 @@ __global__ __launch_bounds__(NT) void k_resident(ResArgs a) {
       double rn = rs;
       if constexpr (X) {
         const double a1 = rho / pqv;
-        const AV t = A::add(A::add(AV{rho, 0.0}, A::times(dot[R], -2.0 * a1)), A::times(A::times(dot[R + 1], a1), a1));
-        rn = A::value(t) > 0.0 ? A::value(t) : 0.0;
+        const DD t = dd_add(dd_add(DD{rho, 0.0}, dd_times(sum[R], -2.0 * a1)), dd_times(dd_times(sum[R + 1], a1), a1));
+        rn = dd_value(t) > 0.0 ? dd_value(t) : 0.0;
       }
       const T be = static_cast<T>(rn / rho);
       rho = rs;

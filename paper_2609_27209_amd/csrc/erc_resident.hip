@@ -65,7 +65,7 @@ ResForm res_form(erc_dtype dt, int64_t n) {
 
 int res_q_place(ResForm f, int64_t n, int nchunk, erc_dtype dt, size_t* lds) {
   const size_t sz = dt == ERC_F32 ? 4 : 8;
-  const size_t red = kResSums * static_cast<size_t>(f.nt / 64) * (dt == ERC_F32 ? sizeof(double) : 2 * sizeof(double));
+  const size_t red = kResSums * static_cast<size_t>(f.nt / 64) * 2 * sizeof(double);
   const size_t p = static_cast<size_t>(f.nt) * f.rpt * sz;
   *lds = red + static_cast<size_t>((nchunk + 1) & ~1) * 8;
   if (res_q_inside(f, sz) && p + *lds + n * sz <= kMaxLds) {
