@@ -203,7 +203,9 @@ erc_status erc_workspace_bytes(erc_handle h, int32_t k_block, size_t* bytes);
  * bytes.  The call blocks until the stream has drained.
  * Graphs of up to 32,768 nodes (16,384 for ERC_F64) with at most 6 MB of positions and
  * weights and few long rows are solved by one launch for all columns that the workspace
- * holds, one workgroup per column, instead of launches per CG iteration.  ERC_PROFILE_SPMM
+ * holds, one workgroup per column, instead of launches per CG iteration (of the larger ones
+ * among them only blocks of 128 columns or the columns of several blocks, which the number of
+ * entries and rows decides).  ERC_PROFILE_SPMM
  * keeps the latter, as there is no SpMM launch to time in the former, and so does plain CG in
  * ERC_F64 with a row of more than 32 entries, whose order of summation it amplifies.
  * Returns ERC_E_NOT_CONVERGED (R still written) when a column hit max_iter above tol,

@@ -86,18 +86,32 @@ static_assert(int64_t{kSampleGrid} * 3 * 8 + int64_t{kSampleGridN} * 8 + 3 * 256
               "the sampling scratch at the grid cap must fit the fixed scratch");
 // Largest operator stream (position and weight bytes per column and iteration) and number of
 // long-row chunks of the resident CG.  A workgroup streams the operator from the L2 by itself
-// and its wavefronts take the chunks in turn, where the block kernels take 30-50 us an
-// iteration on small graphs whatever the size.  Time of the block kernels (graph replay)
-// over that of the resident CG for 16 / 64 / 256 columns in blocks of 64:
-//   2000 rows, 120,000 entries, fp32 unit              2.9 / 2.9 / 8.5
-//   16,000 rows, 320,000 entries, fp32 weighted        1.8 / 1.9 / 6.2   (1.9 MB)
-//   16,000 rows, 320,000 entries, fp64 weighted        1.2 / 1.2 / 2.3   (3.2 MB)
-//   30,000 rows, 990,000 entries, fp32 weighted        0.98 / 1.1 / 2.1  (5.9 MB)
-//   12,000 rows, 190,000 entries, power-law, fp64 weighted   1.1 / 1.7 / 2.9
-// and without the limits, at 9.6 MB about 0.6-0.7 of the block kernels' speed for 16 and 64
-// columns, at 1600 and 4000 chunks 0.4-0.7 and 0.2-0.4.
+// and its wavefronts take the chunks in turn.  At 1600 and 4000 chunks it reached 0.4-0.7 and
+// 0.2-0.4 of the block kernels' speed.
 constexpr int64_t kResMaxStream = 6000000;
 constexpr int64_t kResMaxChunks = 256;
+// An iteration of the resident CG costs the same for 1 to 256 columns, the block kernels' grows
+// with the block's width and runs once per block.  Up to this cost, in units of an unweighted
+// entry (fp32: rows 6, weighted entries 1.5; fp64: rows 45, weighted entries 3.3), the resident
+// CG is the faster one for one narrow block too; above it needs a block of 128 columns or the
+// columns of several blocks.  Time of the block kernels (graph replay) over that of the resident
+// CG for 1 / 16 / 64 columns in one block, 128 in two blocks of 64, 128 in one block:
+//   8000 rows, 732,000 entries, fp32 unit      1.50 / 1.50 / 1.58 / 2.9 / 1.9    (cost 0.78M)
+//   16,000 rows, 990,000, fp32 weighted        1.10 / 1.09 / 1.23 / 2.3 / 1.6    (1.58M)
+//   32,000 rows, 1,343,000, fp32 unit          1.04 / 1.01 / 1.17 / 2.2 / 1.7    (1.54M)
+//   24,000 rows, 1,965,000, fp32 unit          0.90 / 0.90 / 1.05 / 2.0 / 1.6    (2.11M)
+//   32,000 rows, 2,940,000, fp32 unit          0.75 / 0.75 / 0.90 / 1.7 / 1.5    (3.13M)
+//   8000 rows, 335,000, fp64 weighted          1.18 / 1.40 / 1.47 / 2.7 / 1.8    (1.47M)
+//   16,000 rows, 671,000, fp64 unit            1.18 / 1.22 / 1.48 / 2.7 / 2.2    (1.39M)
+//   16,000 rows, 352,000, fp64 weighted        0.78 / 1.00 / 1.06 / 2.0 / 1.6    (1.88M)
+//   8000 rows, 494,000, fp64 weighted          0.78 / 0.96 / 1.06 / 2.0 / 1.4    (1.99M)
+constexpr int64_t kResNarrow32 = 1600000;
+constexpr int64_t kResNarrow64 = 1500000;
+constexpr int kResWide = 128;
+int64_t res_cost(int64_t n, int64_t nnz, bool weighted, erc_dtype dt) {
+  if (dt == ERC_F32) return nnz + (weighted ? nnz / 2 : 0) + 6 * n;
+  return nnz + (weighted ? 23 * nnz / 10 : 0) + 45 * n;
+}
 constexpr int kDefaultCheck = 16;
 // Neighbour-row bytes one SpMM gathers (nnz * kb * element size) above which each CG
 // iteration also enqueues the early stopping test: 4 GB is about half a millisecond of
@@ -1116,15 +1130,20 @@ erc_status solve_resident(erc_graph_s* h, const erc_solve_params* p, Work* w, co
 // where a caller of the fp64 path may look for 1e-9.  The Jacobi variant's few iterations keep
 // such differences to 6e-10 and below.
 constexpr int64_t kResSameOrder = 32;  // rows that the SpMM's lane groups sum one entry after the other
-bool takes_resident(const erc_graph_s* h, const erc_solve_params* p) {
-  if (!h->dg.res.on || (p->flags & ERC_PROFILE_SPMM)) return false;
-  return h->dt == ERC_F32 || (p->flags & ERC_JACOBI) || h->max_degree <= kResSameOrder;
-}
-
 // Columns that one resident solve takes: as many as the workspace's four n x kb arrays hold
 // (once, or twice where q is in memory too) and the widest edge-distance kernel reads.
 int resident_cols(const erc_graph_s* h, int kb) {
   return std::min(h->dg.res.on == 2 ? 2 * kb : 4 * kb, max_width(h->dt));
+}
+
+// `cols` columns in blocks of at most `block`.  (Also where the resident CG would be slower: see
+// res_cost.  Three blocks to two of its launches is where it draws level at the largest cost.)
+bool takes_resident(const erc_graph_s* h, const erc_solve_params* p, int64_t cols, int block) {
+  if (!h->dg.res.on || (p->flags & ERC_PROFILE_SPMM)) return false;
+  if (h->dt == ERC_F64 && !(p->flags & ERC_JACOBI) && h->max_degree > kResSameOrder) return false;
+  if (res_cost(h->n, h->nnz, h->weighted, h->dt) <= (h->dt == ERC_F32 ? kResNarrow32 : kResNarrow64)) return true;
+  const int kb = padded_width(h->dt, block);
+  return kb >= kResWide || 2 * ceil_div(cols, block) >= 3 * ceil_div(cols, resident_cols(h, kb));
 }
 
 erc_status check_handle(const erc_graph_s* h) {
@@ -1394,7 +1413,7 @@ erc_status erc_resistance(erc_handle h, const erc_solve_params* params, void* ws
     ERC_HIP(hipEventRecord(t0, s));
     BlockStats bs;
     int blocks = 0;
-    const bool res = takes_resident(h, params);
+    const bool res = takes_resident(h, params, int64_t{params->col_end} - params->col_begin, params->k_block);
     if (res) {
       const int step = resident_cols(h, kb);
       std::vector<int> iters(params->col_end - params->col_begin);
@@ -1960,7 +1979,7 @@ erc_status erc_debug_solve_block(erc_handle h, const erc_solve_params* params, i
     st = prepare_work(w, s);
     if (st != ERC_OK) return st;
     BlockStats bs;
-    if (takes_resident(h, params))
+    if (takes_resident(h, params, ncols, ncols))
       st = solve_resident(h, params, &w, L, ws_dev, col0, ncols, nullptr, 0, iters_host, &bs, s);
     else
       st = solve_block(h, params, w, col0, ncols, nullptr, 0, iters_host, &bs, s);

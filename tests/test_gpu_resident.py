@@ -129,3 +129,38 @@ def test_fp32_rounds_no_worse_than_block_kernels(n, extra, weighted):
     blk = float((blk - ref).norm() / ref.norm())
     print(f"n={n} extra={extra} weighted={weighted}: resident {res:.2e}, block kernels {blk:.2e}")
     assert res <= 1.2 * blk
+
+
+def _one_launch(info):
+    """A resident solve counts the iterations it took; the block kernels enqueue iterations a
+    group ahead of the host's poll."""
+    return info["launches"] == info["spmm_full"]
+
+
+@pytest.mark.parametrize("n,extra,weighted,dtype,narrow", [
+    (16000, 29.0, True, "f32", True), (24000, 40.0, False, "f32", False), (30000, 15.3, True, "f32", False),
+    (8000, 19.5, True, "f64", True), (16000, 10.0, True, "f64", False), (16000, 45.0, False, "f64", False)])
+def test_solver_by_cost_and_columns(n, extra, weighted, dtype, narrow):
+    """The larger of the graphs with a resident plan take it for wide blocks or several only
+    (kResNarrow32, kResNarrow64, kResWide); all routes agree."""
+    E = _gpu()
+    g = _ring(n, weighted, 41, extra=extra)
+    G = E.Graph(g.rowptr, g.col, g.w, solve_dtype=dtype)
+    tol, bar = (1e-6, 1e-4) if dtype == "f32" else (1e-10, 1e-9)
+    kw = dict(delta=1e-3, tol=tol, seed=3, precond="jacobi")
+    ref, ip = G.resistance(128, 64, profile=True, **kw)
+    assert not _one_launch(ip)
+    one, i1 = G.resistance(128, 128, **kw)
+    two, i2 = G.resistance(128, 64, **kw)
+    # the same columns in calls of one block each
+    acc, ia = G.resistance(128, 64, col_end=64, **kw)
+    acc = acc.clone()
+    _, ib = G.resistance(128, 64, col_begin=64, out=acc, accumulate=True, **kw)
+    assert _one_launch(i1) and _one_launch(i2)
+    assert _one_launch(ia) == _one_launch(ib) == narrow
+    for x in (one, two, acc):
+        assert float(((x - ref).abs() / ref).max()) <= bar
+    _, i3 = G.resistance(128, 16, col_end=48, **kw)  # three blocks of 16
+    assert _one_launch(i3)
+    _, i4 = G.resistance(128, 64, col_end=1, **kw)
+    assert _one_launch(i4) == narrow
