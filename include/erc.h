@@ -264,7 +264,8 @@ erc_status erc_draw_scratch_bytes(erc_handle h, erc_items items, size_t* bytes);
  * integers); draw d takes X = x_hi 2^64 + x_lo with x_hi, x_lo the outputs 2d and 2d+1
  * of SplitMix64 started from the first output of SplitMix64(seed), t = floor(X T / 2^128),
  * and returns the i with C_i <= t < C_{i+1}.  Items with W_i = 0 are never drawn.
- * scratch_dev: >= erc_draw_scratch_bytes bytes.  Blocks until the stream has drained.
+ * scratch_dev: >= erc_draw_scratch_bytes bytes.  idx_dev may overlap prob_dev (slower: the
+ * indices then pass through the host).  Blocks until the stream has drained.
  * ERC_E_NUMERIC (idx_dev filled with -1) when a probability is NaN or outside [0, 1],
  * when they sum above 1.5, or when every W_i is 0. */
 erc_status erc_draw(erc_handle h, erc_items items, const double* prob_dev, int64_t draws,

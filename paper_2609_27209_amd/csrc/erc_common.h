@@ -234,6 +234,7 @@ constexpr uint32_t kSubBadIndex = 8u;      // a drawn index outside the node or 
 constexpr int64_t kScanTile = 4096;        // items per block of a scan
 constexpr int64_t kBitTile = 1024;         // bitmap words per block
 constexpr int64_t kDrawSub = 16;           // items of a subtile of a draw's weights
+constexpr int64_t kDrawSome = 32768;       // draws at a time where they replace the probabilities
 inline int64_t scan_blocks(int64_t items) { return ceil_div(items, kScanTile); }
 // Words of a bitmap over `items`, in whole tiles of at least one.
 inline int64_t sub_words(int64_t items) {
@@ -245,6 +246,7 @@ struct DrawWork {
   uint64_t* tsum;    // scan_blocks(N) + 1: tile sums, then their prefix sums and the total
   double* psum;      // scan_blocks(N) fp64 tile sums of the probabilities
   uint32_t* status;  // one word
+  int64_t* some;     // kDrawSome draws, where idx overlaps the probabilities
 };
 struct SubgraphWork {
   uint32_t* head;       // status, kept nodes, kept edges (followed by the bitmaps)
@@ -256,7 +258,10 @@ struct SubgraphWork {
   uint32_t* tile;       // tile sums
   uint8_t* flags;       // a byte per item (32 per bitmap word), for marks of many items
 };
-hipError_t launch_draw(const double* prob, int64_t N, int64_t draws, uint64_t base,
+// The sums of prob that the draws search; then draws first .. first + draws - 1 into idx, which
+// must not overlap prob (the draws read it).
+hipError_t launch_draw_sums(const double* prob, int64_t N, const DrawWork& w, hipStream_t s);
+hipError_t launch_draw(const double* prob, int64_t N, int64_t first, int64_t draws, uint64_t base,
                        const DrawWork& w, int64_t* idx, hipStream_t s);
 // items 0: subgraph induced on the nodes in idx; 1: the edges in idx and their endpoints
 hipError_t launch_subgraph(const DevGraph& g, int items, const int64_t* idx, int64_t count,

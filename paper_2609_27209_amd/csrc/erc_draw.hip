@@ -194,7 +194,7 @@ __global__ __launch_bounds__(kMidThreads) void k_tile_scan(uint64_t* __restrict_
   }
 }
 
-// One thread per draw.  X = x_hi 2^64 + x_lo from outputs 2d and 2d+1 of SplitMix64 started
+// One thread per draw, draws first .. first + draws - 1.  X = x_hi 2^64 + x_lo from outputs 2d and 2d+1 of SplitMix64 started
 // at `base`; t = floor(X T / 2^128) = hi64(x_hi T + hi64(x_lo T)) is uniform on [0, T), and
 // the drawn item is the last i with C_i <= t: the tile, then its subtile by binary searches of
 // their prefix sums, then the item among the subtile's 16 (two cache lines).  (A group of 16
@@ -203,7 +203,7 @@ __global__ __launch_bounds__(kMidThreads) void k_tile_scan(uint64_t* __restrict_
 __global__ __launch_bounds__(kBlock) void k_draw(const double* __restrict__ P, int64_t N,
                                                  const uint64_t* __restrict__ sub,
                                                  const uint64_t* __restrict__ tsum, int64_t nb,
-                                                 int64_t draws, uint64_t base,
+                                                 int64_t first, int64_t draws, uint64_t base,
                                                  const uint32_t* __restrict__ status,
                                                  int64_t* __restrict__ idx) {
   const uint32_t st = *status;
@@ -214,7 +214,7 @@ __global__ __launch_bounds__(kBlock) void k_draw(const double* __restrict__ P, i
       idx[d] = -1;
       continue;
     }
-    const uint64_t ctr = 2ull * static_cast<uint64_t>(d);
+    const uint64_t ctr = 2ull * static_cast<uint64_t>(first + d);
     const uint64_t xh = sm_final(base + (ctr + 1ull) * kGolden);
     const uint64_t xl = sm_final(base + (ctr + 2ull) * kGolden);
     const uint64_t a_lo = xh * T;
@@ -575,16 +575,20 @@ int blocks_for(int64_t count, int64_t per_block) {
 
 }  // namespace
 
-hipError_t launch_draw(const double* prob, int64_t N, int64_t draws, uint64_t base,
-                       const DrawWork& w, int64_t* idx, hipStream_t s) {
+hipError_t launch_draw_sums(const double* prob, int64_t N, const DrawWork& w, hipStream_t s) {
   const int64_t nb = scan_blocks(N);
   hipError_t e = launch_fill_u32(w.status, 0u, 1, s);
   if (e != hipSuccess) return e;
   ERC_DLAUNCH(k_weight_sums, nb, s, prob, N, w.sub, w.tsum, w.psum, w.status);
   hipLaunchKernelGGL(k_tile_scan, dim3(1), dim3(kMidThreads), 0, s, w.tsum, nb, w.psum, w.status);
-  if (draws > 0)
-    ERC_DLAUNCH(k_draw, blocks_for(draws, kBlock), s, prob, N, w.sub, w.tsum, nb, draws,
-                base, w.status, idx);
+  return hipGetLastError();
+}
+
+hipError_t launch_draw(const double* prob, int64_t N, int64_t first, int64_t draws, uint64_t base,
+                       const DrawWork& w, int64_t* idx, hipStream_t s) {
+  if (draws <= 0) return hipSuccess;
+  ERC_DLAUNCH(k_draw, blocks_for(draws, kBlock), s, prob, N, w.sub, w.tsum, scan_blocks(N), first, draws,
+              base, w.status, idx);
   return hipGetLastError();
 }
 

@@ -1615,7 +1615,7 @@ erc_status erc_sampling_probs_static(erc_handle h, const double* kappa_dev, doub
 
 namespace {
 struct DrawLayout {
-  int64_t sub, tsum, psum, status, total;
+  int64_t sub, tsum, psum, status, some, total;
 };
 DrawLayout draw_layout(int64_t N) {
   DrawLayout L{};
@@ -1630,6 +1630,7 @@ DrawLayout draw_layout(int64_t N) {
   L.tsum = take((nb + 1) * 8);
   L.psum = take(nb * 8);
   L.status = take(4);
+  L.some = take(kDrawSome * 8);
   L.total = off;
   return L;
 }
@@ -1699,7 +1700,25 @@ erc_status erc_draw(erc_handle h, erc_items items, const double* prob_dev, int64
     w.psum = reinterpret_cast<double*>(b + L.psum);
     w.status = reinterpret_cast<uint32_t*>(b + L.status);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    ERC_HIP(launch_draw(prob_dev, N, draws, splitmix_first(seed), w, idx_dev, s));
+    w.some = reinterpret_cast<int64_t*>(b + L.some);
+    const uint64_t base = splitmix_first(seed);
+    ERC_HIP(launch_draw_sums(prob_dev, N, w, s));
+    const char* p0 = reinterpret_cast<const char*>(prob_dev);
+    const char* i0 = reinterpret_cast<const char*>(idx_dev);
+    if (i0 < p0 + N * 8 && p0 < i0 + draws * 8) {
+      // the indices replace probabilities that later draws still read: they wait on the host
+      std::vector<int64_t> all(static_cast<size_t>(draws));
+      for (int64_t d = 0; d < draws; d += kDrawSome) {
+        const int64_t cnt = std::min(kDrawSome, draws - d);
+        ERC_HIP(launch_draw(prob_dev, N, d, cnt, base, w, w.some, s));
+        ERC_HIP(hipMemcpyAsync(all.data() + d, w.some, static_cast<size_t>(cnt) * 8, hipMemcpyDeviceToHost, s));
+        ERC_HIP(hipStreamSynchronize(s));
+      }
+      ERC_HIP(hipMemcpyAsync(idx_dev, all.data(), all.size() * 8, hipMemcpyHostToDevice, s));
+      ERC_HIP(hipStreamSynchronize(s));
+    } else {
+      ERC_HIP(launch_draw(prob_dev, N, 0, draws, base, w, idx_dev, s));
+    }
     const uint32_t* back = nullptr;
     erc_status rs = read_words(h, w.status, 1, s, &back);
     if (rs != ERC_OK) return rs;

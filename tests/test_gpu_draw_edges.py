@@ -1,8 +1,8 @@
 """Draws and subgraphs at the edges of their kernels' shapes, bit for bit against the oracle:
 numbers of items around a subtile (16), a tile (4096) and a bitmap tile (32,768), weights
 concentrated at the ends of tiles, probabilities at an address that is 8- but not 16-byte
-aligned, rows around the 512 entries that a wavefront reads at once, and scratch at an odd
-address."""
+aligned, rows around the 512 entries that a wavefront reads at once, draws around the counts from which marks are bytes and every edge is looked at,
+indices written over the probabilities, and scratch at an odd address."""
 import numpy as np
 import pytest
 
@@ -117,3 +117,21 @@ def test_bad_index_among_many_draws(bad):
     with pytest.raises(_abi.ErcError) as ei:
         G.subgraph("nodes", idx)
     assert ei.value.status == _abi.ERC_E_INVALID_ARG
+
+
+@pytest.mark.parametrize("n,draws,at", [(5000, 5000, 0), (5000, 300, 100), (70000, 69000, 1000), (70000, 32768, 0)])
+def test_indices_in_place_of_probabilities(n, draws, at):
+    E = _gpu()
+    from paper_2609_27209_amd import _abi
+    rng = np.random.default_rng(n)
+    P = rng.random(n)
+    P /= P.sum()
+    G = E.Graph(*(lambda g: (g.rowptr, g.col, g.w))(gen.path_graph(n)))
+    buf = torch.from_numpy(P).cuda()
+    sc = torch.empty(_abi.erc_draw_scratch_bytes(G.handle, _abi.ERC_NODES), dtype=torch.uint8, device="cuda")
+    _abi.erc_draw(G.handle, _abi.ERC_NODES, buf.data_ptr(), draws, 9, sc.data_ptr(), sc.numel(),
+                  buf.data_ptr() + 8 * at, torch.cuda.current_stream().cuda_stream)
+    got = buf.view(torch.int64)[at:at + draws].cpu().numpy()
+    np.testing.assert_array_equal(got, OS.draw(P, draws, 9))
+    rest = np.concatenate([np.arange(at), np.arange(at + draws, n)])
+    np.testing.assert_array_equal(buf.cpu().numpy()[rest], P[rest])
