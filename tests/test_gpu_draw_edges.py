@@ -1,7 +1,8 @@
 """Draws and subgraphs at the edges of their kernels' shapes, bit for bit against the oracle:
 numbers of items around a subtile (16), a tile (4096) and a bitmap tile (32,768), weights
 concentrated at the ends of tiles, probabilities at an address that is 8- but not 16-byte
-aligned, rows around the 512 entries that a wavefront reads at once, draws around the counts from which marks are bytes and every edge is looked at,
+aligned, rows around the 64 entries that a wavefront reads in one step and the 1024 that it reads
+at once, draws around the counts from which marks are bytes and every edge is looked at,
 indices written over the probabilities, and scratch at an odd address."""
 import numpy as np
 import pytest
@@ -135,3 +136,21 @@ def test_indices_in_place_of_probabilities(n, draws, at):
     np.testing.assert_array_equal(got, OS.draw(P, draws, 9))
     rest = np.concatenate([np.arange(at), np.arange(at + draws, n)])
     np.testing.assert_array_equal(buf.cpu().numpy()[rest], P[rest])
+
+
+@pytest.mark.parametrize("degree", [63, 64, 65, 1022, 1023, 1024, 1025, 2047, 2048, 2049, 3073])
+def test_long_rows_of_kept_nodes(degree):
+    """The hub's row and as many of its neighbours as the draws that look at rows allow."""
+    E = _gpu()
+    n = 64 * degree
+    g = _hub_graph(n, degree)
+    G = E.Graph(g.rowptr, g.col, g.w)
+    rng = np.random.default_rng(degree)
+    # fewer than n / 16 draws: the hub, its first and last neighbours, and most of the others
+    kept = np.concatenate([[0, 1, degree, degree - 1], 1 + rng.permutation(degree)[:max(0, n // 16 - 5)]])
+    assert kept.size < n // 16 and np.unique(kept).size > 0.9 * degree
+    idx = rng.permutation(kept)
+    got = G.subgraph("nodes", torch.from_numpy(idx).cuda())
+    want = OS.node_subgraph(g, idx)
+    for k in ("nodes", "edges", "u", "v"):
+        np.testing.assert_array_equal(got[k].cpu().numpy(), want[k])
