@@ -195,12 +195,9 @@ __device__ __forceinline__ V wave_sum(V x) {
 // Makes a uniform address opaque, so that loads through it are not kept in registers across
 // the point (hoisted out of the iteration, or shared between its start and its end): the
 // registers hold z, r and q, and the reloads hit the caches.  The result names its address
-// space, which the compiler would no longer see: global memory, or (for scalar loads)
-// memory that no kernel of the solve writes.
+// space (global memory), which the compiler would no longer see.
 template <typename P>
 using Global = P __attribute__((address_space(1)))*;
-template <typename P>
-using Fixed = const P __attribute__((address_space(4)))*;
 __device__ __forceinline__ uint64_t opaque(const void* p) {
   uint64_t u = reinterpret_cast<uint64_t>(p);
   asm volatile("" : "+s"(u));
@@ -209,10 +206,6 @@ __device__ __forceinline__ uint64_t opaque(const void* p) {
 template <typename P>
 __device__ __forceinline__ Global<P> fresh(P* p) {
   return reinterpret_cast<Global<P>>(opaque(p));
-}
-template <typename P>
-__device__ __forceinline__ Fixed<P> fresh_fixed(const P* p) {
-  return reinterpret_cast<Fixed<P>>(opaque(p));
 }
 __device__ __forceinline__ int fresh_lane(int x) {
   asm volatile("" : "+v"(x));
@@ -265,16 +258,6 @@ __device__ __forceinline__ T at_position(const T* s_p, uint32_t j, int hi) {
     asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0"
         : "=v"(o) : "v"(sizeof(T) == 4 ? 2 : 3), "v"(j));
   return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(s_p) + o);
-}
-
-// Quads [t, t + G) into buf, whether the slot has them or not: loads without a branch
-// between them stay in flight together (the plan keeps kResPadQuads quads past the last).
-template <typename T, bool W, int G>
-__device__ __forceinline__ void load_group(Quad<T, W> (&buf)[G], Global<const uint16_t> idx,
-                                           Global<const T> w, int t, int lane) {
-  static_assert(G <= kResPadQuads, "a group may start at the end of the last slot");
-#pragma unroll
-  for (int g = 0; g < G; ++g) buf[g] = load_quad<T, W>(idx, w, t + g, lane);
 }
 
 template <int N>
