@@ -121,7 +121,7 @@ constexpr double kFin2MinGather = 4e9;
 size_t dsize(erc_dtype t) { return t == ERC_F32 ? 4 : 8; }
 int64_t align_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
 
-// Sizes that depend only on (n, nnz): the plan shape and upper bounds of its lists.
+// Sizes that the row pointers give: the plan shape and upper bounds of its lists.
 struct Shape {
   int64_t n, nnz, m;
   double share;      // target cost per wave
@@ -131,9 +131,13 @@ struct Shape {
   int64_t ntask_max, nmega_max, nslot_max;
   ResForm res;       // form of the resident CG (0 slots: the graph is too large for it)
   int64_t quads_max, hchunk_max;
+  bool res_long;     // it has rows of more than kResHeavy entries
 };
 
-Shape make_shape(int64_t n, int64_t nnz, bool weighted, erc_dtype dt) {
+Shape make_shape(const erc_graph_desc* d) {
+  const int64_t n = d->n, nnz = d->rowptr[n];
+  const bool weighted = d->w != nullptr;
+  const erc_dtype dt = d->solve_dtype;
   Shape s{};
   s.n = n;
   s.nnz = nnz;
@@ -163,6 +167,7 @@ Shape make_shape(int64_t n, int64_t nnz, bool weighted, erc_dtype dt) {
     // is at most 64 rows of kResHeavy entries plus nnz; each slot rounds up to four entries
     s.quads_max = ceil_div(64 * kResHeavy + nnz + int64_t{3} * s.res.nt * s.res.rpt, 256) + kResPadQuads;
     s.hchunk_max = kResMaxChunks;
+    for (int64_t i = 0; i < n; ++i) s.res_long = s.res_long || d->rowptr[i + 1] - d->rowptr[i] > kResHeavy;
   }
   return s;
 }
@@ -211,7 +216,7 @@ GraphLayout graph_layout(const Shape& s, bool weighted, erc_dtype dt) {
     L.res_hc0 = take((s.hchunk_max + 1) * 4);
     L.res_idx = take(s.quads_max * 512);
     L.res_w = take(weighted ? s.quads_max * 256 * sz : 0);
-    L.res_cpos = take(s.nnz * 2);
+    L.res_cpos = take(s.res_long ? s.nnz * 2 : 0);
   }
   L.eu = take(s.m * 4);
   L.ev = take(s.m * 4);
@@ -1193,7 +1198,7 @@ erc_status erc_graph_bytes(const erc_graph_desc* desc, size_t* bytes) {
     erc_status st = check_desc(desc);
     if (st != ERC_OK) return st;
     if (bytes == nullptr) return fail(ERC_E_INVALID_ARG, "bytes is NULL");
-    const Shape s = make_shape(desc->n, desc->rowptr[desc->n], desc->w != nullptr, desc->solve_dtype);
+    const Shape s = make_shape(desc);
     *bytes = static_cast<size_t>(graph_layout(s, desc->w != nullptr, desc->solve_dtype).total);
     return ERC_OK;
   });
@@ -1213,7 +1218,7 @@ erc_status erc_create(const erc_graph_desc* desc, void* dev_mem, size_t bytes, v
     if (st != ERC_OK) return st;
     const int64_t n = desc->n;
     const int64_t nnz = desc->rowptr[n];
-    const Shape s = make_shape(n, nnz, desc->w != nullptr, desc->solve_dtype);
+    const Shape s = make_shape(desc);
     const bool weighted = desc->w != nullptr;
     const GraphLayout L = graph_layout(s, weighted, desc->solve_dtype);
     if (static_cast<int64_t>(bytes) < L.total)
@@ -1832,7 +1837,7 @@ erc_status erc_debug_check_plan(const erc_graph_desc* desc) {
     const int64_t n = desc->n;
     const int64_t* rp = desc->rowptr;
     const int64_t nnz = rp[n];
-    const Shape s = make_shape(n, nnz, desc->w != nullptr, desc->solve_dtype);
+    const Shape s = make_shape(desc);
     Plan P;
     build_plan(desc, s, &P);
     auto bad = [&](const std::string& what) { return fail(ERC_E_STATE, "plan check: " + what); };
@@ -1902,7 +1907,7 @@ erc_status erc_debug_check_plan(const erc_graph_desc* desc) {
       for (int32_t p = 0; p < P.res_nheavy; ++p) {
         int64_t next = rp[P.res_row[p]];
         for (int32_t k = P.res_hc0[p]; k < P.res_hc0[p + 1]; ++k) {
-          if (P.res_hpos[k] != p || P.res_hbeg[k] != next || P.res_hlen[k] < 1 || P.res_hlen[k] > kResChunk)
+          if (!s.res_long || P.res_hpos[k] != p || P.res_hbeg[k] != next || P.res_hlen[k] < 1 || P.res_hlen[k] > kResChunk)
             return bad("resident chunk");
           next += P.res_hlen[k];
         }

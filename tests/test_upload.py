@@ -67,3 +67,22 @@ def test_operator_and_solve_on_weighted_trees(n, dtype):
     ref, _ = OE.resistance(g, 4, 4, delta, tol, 10000, 3, dtype)
     assert info["cols_unconverged"] == 0 and info["breakdowns"] == 0
     assert np.max(np.abs(R.cpu().numpy() - ref) / ref) <= bar
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+def test_positions_for_long_rows_only_where_there_are_any(dtype):
+    """Two bytes per entry, which only rows of more than 128 entries read."""
+    import paper_2609_27209_amd as E
+    from paper_2609_27209_amd import _abi
+    n, k = 3000, 127
+    ring = np.arange(n)
+    size = []
+    for at in (0, 1):  # node 0 with 2 + 126 and with 2 + 127 entries, as many entries in all
+        u = np.concatenate([ring, np.full(k - 1 + at, 0), np.arange(1, 2 - at)])
+        v = np.concatenate([(ring + 1) % n, 100 + np.arange(k - 1 + at), 1000 + np.arange(1, 2 - at)])
+        g = gen.from_edges(n, u, v)
+        assert g.nnz == 2 * (n + k) and np.diff(g.rowptr).max() == 128 + at
+        d, keep = E._desc(g.rowptr, g.col, g.w, dtype)
+        size.append(_abi.erc_graph_bytes(d))
+        del keep
+    assert size[1] - size[0] == -(-2 * g.nnz // 256) * 256
