@@ -141,7 +141,11 @@ typedef struct {
   uint32_t flags;
 } erc_solve_params;
 
-/* Filled by erc_resistance when non-NULL. */
+/* Filled by erc_resistance when non-NULL.  Graphs solved by a single launch (see
+ * erc_resistance) launch no SpMM: there `launches` and `spmm_full` count, for each block of
+ * k_block columns, the most iterations that one of its columns took, and `bytes_model` is
+ * what per-iteration launches would have moved for them: equivalents for comparing work, of
+ * which no rate of that launch follows. */
 typedef struct {
   int32_t blocks;             /* column blocks solved                                */
   int32_t iters_max;          /* largest per-column iteration count                  */

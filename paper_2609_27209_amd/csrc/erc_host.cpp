@@ -1429,7 +1429,7 @@ erc_status erc_resistance(erc_handle h, const erc_solve_params* params, void* ws
                             iters.data() + (c0 - params->col_begin), &bs, s);
         if (st != ERC_OK) return st;
       }
-      // blocks of the caller's width, and the iterations of each, as the block solver counts
+      // the block kernels' equivalent: blocks of the caller's width and the iterations of each
       for (size_t c = 0; c < iters.size(); c += params->k_block) {
         const auto b = iters.begin() + c;
         const auto e = iters.begin() + std::min(iters.size(), c + params->k_block);
