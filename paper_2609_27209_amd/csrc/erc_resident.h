@@ -8,26 +8,26 @@
 // launch, grid-wide reduction or host poll sits between iterations.
 //
 // What bounds it: on the smallest graphs the chain of reductions, barriers and LDS round
-// trips of an iteration (2000 rows: 3.7 us in fp32, 4.9 us in fp64), on larger ones the LDS
-// gathers, whose random banks collide (64-lane gathers take 7 cycles instead of 2), and the
-// vector instructions around them (20,000 rows, 220,000 entries: 20.6 us; LDS busy 61% of
-// the time, over half of it conflicts, vector units 49%), with the operator's stream from the
-// L2 (2 bytes of position and the weight per entry) behind them.  The block kernels took 28,
+// trips of an iteration (2000 rows, 22,000 entries: 4.0 us in fp32, 4.8 us in fp64), on larger
+// ones the LDS gathers, whose random banks collide (64-lane gathers take 7 cycles instead of
+// 2), and the vector instructions around them (20,000 rows, 220,000 entries: 20.9 us; LDS busy
+// 58% of the time, over half of it conflicts, vector units 64%), with the operator's stream from
+// the L2 (2 bytes of position and the weight per entry) behind them.  The block kernels took 28,
 // 28 and 54 us for these iterations of 32, 64 and 64 columns, as three or four dependent
-// launches each.  Whole steps: 2000 rows fp64 1.19 -> 0.35 ms, 2000 rows and 1024 columns
-// 16.5 -> 0.70 ms, 20,000 rows 1.95 -> 0.92 ms, 12,305 rows fp64 Jacobi 4.8 -> 1.3 ms.
+// launches each.  Whole steps: 2000 rows fp64 1.19 -> 0.34 ms, 2000 rows and 1024 columns
+// 16.7 -> 0.76 ms, 20,000 rows 1.99 -> 0.97 ms, 12,305 rows fp64 Jacobi 4.7 -> 1.27 ms.
 //
 // The recurrence is Hestenes-Stiefel CG with the stopping rule of the block kernels, and no sum
 // is less precise than theirs: fp32 or fp64 vectors; a thread's part of an inner product in fp64
 // or double-double, the threads' parts folded as compensated pairs; in fp32 a row's entries in
 // fours, and the fours (of rows above kResHeavy entries each entry) added in fp64.  (fp32 chains
 // over the row put weighted rows of about 100 entries 1.7 times as far from the fp64 solution
-// as the block kernels, and plain folds saved 0.5 us an iteration.)  In fp64 beta also has
-// their expanded form, so that rows which both sum one entry after the other give the same bits
-// from both (fp64 CG is where a caller looks for agreement beyond the stopping tolerance, and a
-// few ten iterations amplify the last bit of a beta to 1e-8 of the solution); fp32 takes r.r of
-// the stored r, which needs slightly fewer iterations on power-law graphs than the expansion and
-// lies no further from the fp64 solution.
+// as the block kernels; with plain folds they saved 0.4-0.7 us an iteration up to 16,384 rows
+// and 1.1-1.5 us above.)  In fp64 beta also has their expanded form, so that rows which both sum
+// one entry after the other give the same bits from both (fp64 CG is where a caller looks for
+// agreement beyond the stopping tolerance, and a few ten iterations amplify the last bit of a
+// beta to 1e-8 of the solution); fp32 takes r.r of the stored r, which needs slightly fewer
+// iterations on power-law graphs than the expansion and lies no further from the fp64 solution.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -66,6 +66,16 @@ inline constexpr ResForm kForms64[] = {{512, 2}, {512, 4}, {1024, 4}, {1024, 6},
 constexpr int kResRegQuads = 16;
 // Sums of a workgroup that the LDS has room for: four of an update and p.q.
 constexpr int kResSums = 5;
+// Sums that a workgroup folds at once, of which the LDS holds a part per thread where res_parts.
+constexpr int kResFolds = 2;
+
+// Forms whose partial sums go through the LDS to one wavefront per sum (fp32 up to 16,384 rows)
+// rather than being folded by every wavefront in registers: 120 instructions per sum and
+// wavefront, four wavefronts to a SIMD, of a short iteration.  Up to 12,288 rows that saves
+// 0.5-0.8 us of an iteration (8000 rows, 88,000 entries: 9.85 -> 9.1 us, with Jacobi 12.3 ->
+// 11.0), at 16,000 0.5 of 16.5 us, above nothing (20,000 rows with Jacobi 27.4 -> 29.6 us, as q
+// no longer fits beside the parts); fp64's pairs would need twice the LDS.
+constexpr bool res_parts(ResForm f, size_t elem) { return elem == 4 && f.nt * f.rpt <= 16 * 1024; }
 
 // Places for q that a form's kernels exist for: beside p in the LDS (a form's last rows may be
 // missing, which leaves room), and outside it.
@@ -192,6 +202,22 @@ template <typename V>
 __device__ __forceinline__ V wave_sum(V x) {
   return across<32>(across<16>(row_sum<16>(x)));
 }
+
+// The sum of N parts as a compensated pair, by halves.
+template <int N>
+__device__ __forceinline__ DD pair_of(const double (&x)[N]) {
+  static_assert(N == 8 || N == 16, "parts per lane");
+  DD t[N / 2];
+#pragma unroll
+  for (int k = 0; k < N / 2; ++k) two_sum(x[k], x[k + N / 2], t[k].s, t[k].c);
+#pragma unroll
+  for (int h = N / 4; h > 0; h >>= 1) {
+#pragma unroll
+    for (int k = 0; k < h; ++k) t[k] = dd_add(t[k], t[k + h]);
+  }
+  return t[0];
+}
+
 // Makes a uniform address opaque, so that loads through it are not kept in registers across
 // the point (hoisted out of the iteration, or shared between its start and its end): the
 // registers hold z, r and q, and the reloads hit the caches.  The result names its address
@@ -280,7 +306,9 @@ __global__ __launch_bounds__(NT) void k_resident(ResArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   DD (*s_red)[NW] = reinterpret_cast<DD (*)[NW]>(smem);
   double* s_h = reinterpret_cast<double*>(&s_red[kResSums][0]);
-  T* s_q = reinterpret_cast<T*>(s_h + ((a.p.nchunk + 1) & ~1));
+  constexpr bool PARTS = res_parts(ResForm{NT, RPT}, sizeof(T));
+  double* s_part = s_h + ((a.p.nchunk + 1) & ~1);  // kResFolds x NT where PARTS
+  T* s_q = reinterpret_cast<T*>(s_part + (PARTS ? kResFolds * NT : 0));
 
   int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -292,17 +320,36 @@ __global__ __launch_bounds__(NT) void k_resident(ResArgs a) {
   const int ends = a.p.off[wv * RPT + min(lane + 1, RPT)];
 
   // sums over the workgroup of K values at once, in every thread; partial set b is free
-  // again when the barrier after the next has passed (set 0: up to four sums, set 1: one)
+  // again when the barrier after the next has passed (set 0: up to four sums, set 1: one).
+  // Every wavefront folds its lanes' pairs and then the wavefronts', or (PARTS) one wavefront per
+  // value adds NT / 64 threads' parts per lane before it folds.
   auto block_sums = [&](const typename A::L* x, DD* sum, auto kk, int b) {
     constexpr int K = decltype(kk)::value;
+    if constexpr (PARTS) {
+      static_assert(K <= kResFolds, "room for the parts");
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-      const DD t = wave_sum(A::pair(x[k]));
-      if (lane == 0) s_red[4 * b + k][wv] = t;
+      for (int k = 0; k < K; ++k) s_part[k * NT + tid] = x[k];
+      __syncthreads();
+      if (wv < K) {
+        double part[NW];
+#pragma unroll
+        for (int k = 0; k < NW; ++k) part[k] = s_part[wv * NT + k * 64 + lane];
+        const DD t = wave_sum(pair_of(part));
+        if (lane == 0) s_red[4 * b + wv][0] = t;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < K; ++k) sum[k] = s_red[4 * b + k][0];
+    } else {
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        const DD t = wave_sum(A::pair(x[k]));
+        if (lane == 0) s_red[4 * b + k][wv] = t;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < K; ++k) sum[k] = row_sum<NW>(s_red[4 * b + k][lane & (NW - 1)]);
     }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < K; ++k) sum[k] = row_sum<NW>(s_red[4 * b + k][lane & (NW - 1)]);
   };
   static_assert(NW == 8 || NW == 16, "row_sum adds 8 or 16 partials");
 

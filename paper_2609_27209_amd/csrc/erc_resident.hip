@@ -67,7 +67,8 @@ int res_q_place(ResForm f, int64_t n, int nchunk, erc_dtype dt, size_t* lds) {
   const size_t sz = dt == ERC_F32 ? 4 : 8;
   const size_t red = kResSums * static_cast<size_t>(f.nt / 64) * 2 * sizeof(double);
   const size_t p = static_cast<size_t>(f.nt) * f.rpt * sz;
-  *lds = red + static_cast<size_t>((nchunk + 1) & ~1) * 8;
+  const size_t parts = res_parts(f, sz) ? kResFolds * static_cast<size_t>(f.nt) * 8 : 0;
+  *lds = red + static_cast<size_t>((nchunk + 1) & ~1) * 8 + parts;
   if (res_q_inside(f, sz) && p + *lds + n * sz <= kMaxLds) {
     *lds += n * sz;
     return 1;
