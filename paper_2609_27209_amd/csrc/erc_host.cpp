@@ -626,7 +626,7 @@ struct Upload {
 
 // Arrays that follow each other within kStage bytes go up in one copy, from a host buffer of
 // their own: a copy costs about 10 us whatever its size, and a small graph has some twenty
-// arrays (2000 nodes: 0.75 -> 0.6 ms per erc_create).  Arrays above kStage / 2 go up by
+// arrays (2000 nodes: 0.42 -> 0.34 ms per graph made).  Arrays above kStage / 2 go up by
 // themselves, and end the buffer before them: a buffer holds the gaps between its arrays too,
 // so that one which went on behind such an array would carry its place along.
 void gather_copies(Upload* U) {
