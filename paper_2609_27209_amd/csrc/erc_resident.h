@@ -7,12 +7,14 @@
 // q in registers, the two inner products of an iteration by workgroup reductions.  No
 // launch, grid-wide reduction or host poll sits between iterations.
 //
-// What bounds it: on the smallest graphs the chain of reductions, barriers and LDS round
-// trips of an iteration (2000 rows, 22,000 entries: 4.0 us in fp32, 4.8 us in fp64), on larger
-// ones the LDS gathers, whose random banks collide (64-lane gathers take 7 cycles instead of
-// 2), and the vector instructions around them (20,000 rows, 220,000 entries: 20.9 us; LDS busy
-// 58% of the time, over half of it conflicts, vector units 64%), with the operator's stream from
-// the L2 (2 bytes of position and the weight per entry) behind them.  The block kernels took 28,
+// What bounds it: on the smallest graphs in fp32 the chain of reductions, barriers and LDS
+// round trips of an iteration (2000 rows, 22,000 entries: 3.7 us; vector units and LDS busy 36%
+// of the time each), in fp64 the vector instructions of the double-double products and folds
+// (4.8 us; vector units 68%), on larger graphs the LDS gathers, whose random banks collide
+// (64-lane gathers take 7 cycles instead of 2), and the vector instructions around them (20,000
+// rows, 220,000 entries: 20.7 us; LDS busy 58% of the time, over half of it conflicts, vector
+// units 64%), with the operator's stream from the L2 (2 bytes of position and the weight per
+// entry) behind them.  The block kernels took 28,
 // 28 and 54 us for these iterations of 32, 64 and 64 columns, as three or four dependent
 // launches each.  Whole steps: 2000 rows fp64 1.19 -> 0.34 ms, 2000 rows and 1024 columns
 // 16.7 -> 0.76 ms, 20,000 rows 1.99 -> 0.97 ms, 12,305 rows fp64 Jacobi 4.7 -> 1.27 ms.
