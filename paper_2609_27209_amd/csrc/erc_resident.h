@@ -14,10 +14,10 @@
 // (64-lane gathers take 7 cycles instead of 2), and the vector instructions around them (20,000
 // rows, 220,000 entries: 20.7 us; LDS busy 58% of the time, over half of it conflicts, vector
 // units 64%), with the operator's stream from the L2 (2 bytes of position and the weight per
-// entry) behind them.  The block kernels took 28,
-// 28 and 54 us for these iterations of 32, 64 and 64 columns, as three or four dependent
-// launches each.  Whole steps: 2000 rows fp64 1.19 -> 0.34 ms, 2000 rows and 1024 columns
-// 16.7 -> 0.76 ms, 20,000 rows 1.99 -> 0.97 ms, 12,305 rows fp64 Jacobi 4.7 -> 1.27 ms.
+// entry) behind them.  The block kernels took 28, 28 and 54 us for these iterations of 32, 64
+// and 64 columns, as three or four dependent launches each.  Whole steps: 2000 rows fp64 1.20 ->
+// 0.34 ms, 2000 rows and 1024 columns 16.7 -> 0.79 ms, 20,000 rows 2.00 -> 0.97 ms, 12,305 rows
+// fp64 Jacobi 4.7 -> 1.27 ms.
 //
 // The recurrence is Hestenes-Stiefel CG with the stopping rule of the block kernels, and no sum
 // is less precise than theirs: fp32 or fp64 vectors; a thread's part of an inner product in fp64
