@@ -72,6 +72,8 @@ CASES = {
     "degrees_127_to_129": lambda wt: _hubs(3000, [125, 126, 127, 128, 129], wt, 7),
     "chunked_rows": lambda wt: _hubs(5000, [255, 256, 257, 513, 4000], wt, 8),
     "dense": lambda wt: _ring(300, wt, 9, extra=60.0),
+    # the fullest LDS: p, q, a part per thread of two sums, and 240 chunk sums
+    "n16384_chunked_rows": lambda wt: _hubs(16384, [4000] * 15, wt, 15),
     "n16384": lambda wt: _ring(16384, wt, 10, extra=1.0),
     "n16385": lambda wt: _ring(16385, wt, 11, extra=1.0),
     "n32768": lambda wt: _ring(32768, wt, 12, extra=1.0),
